@@ -305,15 +305,14 @@ int leech_gemv(const leech_layout_desc* desc, const void* d_main, const void* d_
 
 /* Batched GEMV (§6 "Batching": one decode of each weight serves several
  * activations): Y[b] = W X[b] for b < batch, X[b] binary16 [Kpad] at
- * d_X + b·ldx, Y[b] f32 [M] at d_Y + b·ldy.  Each block is decoded once per
- * launch and multiplied with up to 16 activations staged in LDS; larger
- * batches run in chunks of 16 (fewer where Kpad leaves too little LDS: 16
- * activations fit up to about Kpad = 4,600, 8 up to about 9,200, the exact
- * bound depending on the column groups' rounding; where not even two fit,
- * the vectors run as single GEMVs).  Products as leech_set_batch_mode
- * selects: on the matrix cores (the default) Y[b][r] is within rounding of
- * leech_gemv on X[b] (tested within 2^-15 · Σ_j |W_rj · X[b]_j|), and a single
- * vector left after the 16-wide chunks still runs 2 wide; with v_dot2 Y[b]
+ * d_X + b·ldx, Y[b] f32 [M] at d_Y + b·ldy.  Products as
+ * leech_set_batch_mode selects.  On the matrix cores (the default) a batch is
+ * one launch, which decodes each block once per tile of up to 64 activations;
+ * Y[b][r] is within rounding of leech_gemv on X[b] (tested within 2^-15 ·
+ * Σ_j |W_rj · X[b]_j|).  With v_dot2 a launch takes up to 16 activations staged
+ * in LDS (fewer where Kpad leaves too little: 16 fit up to about Kpad = 4,600,
+ * 8 up to about 9,200, the exact bound depending on the column groups'
+ * rounding; where not even two fit, the vectors run as single GEMVs), and Y[b]
  * is bit-identical to leech_gemv on X[b].  batch > 1 serves
  * LEECH_PLANES14 (LEECH_E_LAYOUT otherwise) and needs ldx ≥ Kpad, ldx a
  * multiple of 8 and ldy ≥ M (LEECH_E_ARG); batch = 1 is leech_gemv.  Other

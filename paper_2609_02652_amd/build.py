@@ -15,7 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libleech.so")
 SOURCES = [os.path.join(CSRC, "host.cpp"), os.path.join(CSRC, "kernels.hip"),
-           os.path.join(CSRC, "rotate.hip"), os.path.join(CSRC, "transcode.hip")]
+           os.path.join(CSRC, "batch.hip"), os.path.join(CSRC, "rotate.hip"),
+           os.path.join(CSRC, "transcode.hip")]
 ARCH = os.environ.get("LEECH_OFFLOAD_ARCH", "gfx950")
 
 

@@ -42,8 +42,6 @@
 // block's factor 2^24 · scale · centroid[gain] / (4√m) is applied once per
 // block.
 
-#include <hip/hip_runtime.h>
-
 #include <atomic>
 #include <cmath>
 #include <cstdint>
@@ -52,16 +50,11 @@
 #include <string>
 #include <type_traits>
 
+#include "batch.h"
+#include "device_common.h"
 #include "leech_internal.h"
 
 namespace leech {
-
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x3 __attribute__((ext_vector_type(3), aligned(4)));
-typedef uint32_t u32x4a __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2a __attribute__((ext_vector_type(2)));
-typedef float f32x4a __attribute__((ext_vector_type(4)));
 
 constexpr int kNoWeights = 99;   // layout id of the no-weights control
 // Prologue modes of the GEMV (the host picks one from the units each wave
@@ -74,17 +67,11 @@ constexpr int kNoWeights = 99;   // layout id of the no-weights control
 //   PRO 1: 3 of 8 before it;   PRO 2: 2 of 6 (waves with ≤ 6 units).
 __host__ __device__ constexpr int pro_prefetch(int pro) { return pro == 2 ? 6 : 8; }
 __host__ __device__ constexpr int pro_first(int pro) { return pro == 0 ? 8 : pro == 1 ? 3 : 2; }
-constexpr float kTwo24 = 16777216.0f;
 // Waves per GEMV workgroup, at most: 8 waves leave each lane up to 256 VGPRs,
 // so the eight prefetch slots and the exception-path decode stay in registers.
 constexpr int kMaxWaves = 8;
 // Exception entries a thread holds in registers from the prologue
 constexpr int kExcPrefetch = 4;
-constexpr int kTableBytes = 1024 * 16;    // LDS class-table entries (class | gain << 9)
-// Raw buffer descriptor, word 3, for the gfx9 family (32-bit elements, no
-// swizzle); loads carry the non-temporal hint: records and scales are read once.
-constexpr int kRsrcWord3 = 0x00020000;
-constexpr int kStreamed = 2;
 
 template <int LAYOUT> struct Stride { static constexpr uint32_t v = 0; };
 template <> struct Stride<LEECH_PLANES14> { static constexpr uint32_t v = kPlanes14Bytes; };
@@ -173,25 +160,10 @@ struct LdsSide {
   }
 };
 
-// Per-(class, gain) entry staged in LDS at byte (class | gain << 9) · 16.
-struct LdsEntry {
-  uint32_t tlo, thi;    // v_perm table (DevClass::perm; Planes12x: see p12_core;
-                        // Golay70: see golay70_core)
-  float factor;         // 2^24 · centroid[gain] / (4√m)
-  uint32_t aux;         // Slot32: level count; Planes12x, Golay70: f32 added to the
-                        // block's sum × factor (0, or an exception's kept contribution)
-};
-static_assert(sizeof(LdsEntry) * 1024 == kTableBytes, "table entries are 16 bytes");
 // Golay70 in LDS: the generator table, and each class's Planes14 table (for
 // an exception's exact record)
 constexpr int kG70LdsBytes = 128 * 4 + 512 * 8;
 
-__device__ __forceinline__ uint32_t align(uint32_t hi, uint32_t lo, uint32_t s) {
-  return __builtin_amdgcn_alignbit(hi, lo, s);
-}
-__device__ __forceinline__ uint32_t perm(uint32_t s0, uint32_t s1, uint32_t sel) {
-  return __builtin_amdgcn_perm(s0, s1, sel);
-}
 // (m & a) | (~m & b) as one v_bfi_b32: left to itself the compiler splits the
 // nibble transpose's bit-field inserts into and / and_or pairs.
 __device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) {
@@ -212,14 +184,6 @@ __device__ __forceinline__ uint32_t lshl4_add(uint32_t a, uint32_t b) {
   uint32_t r;
   asm("v_lshl_add_u32 %0, %1, 4, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
-}
-// Reinterpret a 32-bit word as two binary16 values.  Takes the word by value:
-// applying __builtin_bit_cast directly to an ext_vector element (w.y) reads
-// element 0 with this compiler, so vector elements go through this function.
-__device__ __forceinline__ half2_t as_h2(uint32_t v) { return __builtin_bit_cast(half2_t, v); }
-
-__device__ __forceinline__ _Float16 as_half(uint32_t h) {
-  return __builtin_bit_cast(_Float16, (uint16_t)h);
 }
 
 // 4×4 bit transpose inside every nibble: on return n[r] bit (4g + q) is bit
@@ -299,24 +263,6 @@ __device__ __forceinline__ void g70_table(const u32x4a& v, uint32_t& tlo, uint32
   thi = (uint32_t)v.w | ((uint32_t)v.y & 0x80808080u);
 }
 
-// Coordinates of pair k of h[] (and of the staged x pairs).
-__host__ __device__ constexpr void pair_coords(int k, int& c0, int& c1) {
-  const int r = k / 3, m = k % 3;
-  c0 = m == 0 ? r : (m == 1 ? 4 + r : 8 + r);
-  c1 = m == 0 ? 16 + r : (m == 1 ? 20 + r : 12 + r);
-}
-// The Planes14 record stores its pairs in the host's kPairCoords order, which
-// must be this one.
-__host__ __device__ constexpr bool pair_order_matches_records() {
-  for (int k = 0; k < 12; ++k) {
-    int c0 = 0, c1 = 0;
-    pair_coords(k, c0, c1);
-    if (c0 != kPairCoords[k][0] || c1 != kPairCoords[k][1]) return false;
-  }
-  return true;
-}
-static_assert(pair_order_matches_records(), "pair order of the kernels and the records");
-
 // ---------------------------------------------------------- per-block reads
 // A lane's place in a unit: its position ul (0 for a lane without a block,
 // which then reads block 0 as a stand-in) and, for the fixed-stride layouts,
@@ -344,32 +290,6 @@ struct Pref {
   uint32_t scale;
   uint32_t sh, esh;
 };
-
-// Planes14 record in the four-word window whose record starts at bit sh (0
-// or 16): each pair word starts on a 32-bit boundary of the record, so one
-// funnel shift each gives it; e16 = (class | gain << 9)·16, the entry's LDS
-// byte address.  Pair q = 4w + k of word w is its rotation by 4k masked with
-// 0x08070807, which is already the byte-permute selector of the pair's two
-// binary16 values (the store order of the record): no transpose, no pair
-// gathering.
-__device__ __forceinline__ void p14_record(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
-                                           uint32_t sh, uint32_t esh, uint32_t W[3],
-                                           uint32_t& e16) {
-  W[0] = align(w1, w0, sh);
-  W[1] = align(w2, w1, sh);
-  W[2] = align(w3, w2, sh);
-  e16 = align(w3, w3, esh) & 0x3FF0u;
-}
-__device__ __forceinline__ void p14_core(const uint32_t W[3], uint32_t tlo, uint32_t thi,
-                                         uint32_t h[12]) {
-#pragma unroll
-  for (int w = 0; w < 3; ++w)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t s = k ? align(W[w], W[w], 4 * k) : W[w];
-      h[4 * w + k] = perm(thi, tlo, s & 0x08070807u);
-    }
-}
 
 // Planes12x core: the 12 pair selector words taken straight from the
 // record's words (one funnel shift or rotation each, kP12Sel), each masked to
@@ -470,11 +390,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t null_rsrc() {
   return __builtin_amdgcn_make_buffer_rsrc(nullptr, 0, 0, kRsrcWord3);
 }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint64_t bytes) {
-  const uint32_t n = bytes > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, kRsrcWord3);
-}
-
 // Loads of unit g for a lane at place L.  EVEN: every unit base of the layout
 // is 4-aligned, so L is used as is; otherwise the lane's window is recomputed
 // from the unit base's offset modulo 4.  Loads are issued unconditionally:
@@ -524,18 +439,6 @@ __device__ __forceinline__ Pref load_unit(const GemvArgs& a, const TileCtx& t, b
   }
 }
 
-// The LDS entries, built from the device table: one 16-byte load per entry.
-__device__ __forceinline__ LdsEntry make_entry(const DevClass* tab, uint32_t e, float cen0,
-                                               float cen1) {
-  const u32x4a d = *(const u32x4a*)&tab[e & 511u];      // perm[8], inv_norm, info
-  LdsEntry t;
-  t.tlo = d.x;
-  t.thi = d.y;
-  t.factor = __builtin_bit_cast(float, (uint32_t)d.z) * kTwo24 * ((e >> 9) ? cen1 : cen0);
-  t.aux = d.w & 0xFFu;
-  return t;
-}
-
 // Planes12x entries: tlo holds the Planes14 table's high word (|z| of
 // levels 3 and 4), thi the magnitudes p12_core reads (levels 0..3), aux the
 // added term (0 for a class).  p12_as14 rebuilds the Planes14 table, for an
@@ -570,34 +473,6 @@ __device__ __forceinline__ LdsEntry make_entry_as(const DevClass* tab, uint32_t 
 // Golay codeword of a 12-bit message from the 128-entry generator table.
 __device__ __forceinline__ uint32_t golay_word(const uint32_t* gen, uint32_t m) {
   return gen[m & 63u] ^ gen[64u + (m >> 6)];
-}
-
-// x of block j in the cores' pair order: three 16-byte loads, then pair k
-// (coordinates pair_coords(k)) picked by one v_perm_b32 each.
-struct XBlock {
-  u32x4a v0, v1, v2;
-};
-__device__ __forceinline__ XBlock load_x_block(const uint16_t* xj) {
-  const u32x4a* src = (const u32x4a*)xj;
-  return XBlock{src[0], src[1], src[2]};
-}
-__device__ __forceinline__ void store_x_block(const XBlock& xb, uint32_t* dst) {
-  const uint32_t w[12] = {xb.v0.x, xb.v0.y, xb.v0.z, xb.v0.w, xb.v1.x, xb.v1.y,
-                          xb.v1.z, xb.v1.w, xb.v2.x, xb.v2.y, xb.v2.z, xb.v2.w};
-  uint32_t o[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    int c0, c1;
-    pair_coords(k, c0, c1);
-    // low half: half c0 % 2 of word c0 / 2 (selector bytes 0..3 pick S1);
-    // high half: half c1 % 2 of word c1 / 2 (bytes 4..7 pick S0)
-    const uint32_t sel = (c0 & 1 ? 0x0302u : 0x0100u) | (c1 & 1 ? 0x07060000u : 0x05040000u);
-    o[k] = perm(w[c1 >> 1], w[c0 >> 1], sel);
-  }
-  u32x4a* d = (u32x4a*)dst;
-  d[0] = u32x4a{o[0], o[1], o[2], o[3]};
-  d[1] = u32x4a{o[4], o[5], o[6], o[7]};
-  d[2] = u32x4a{o[8], o[9], o[10], o[11]};
 }
 
 // s = Σ_k h[k]·x[k] over the 12 binary16 pairs, f32 accumulation; the first
@@ -1404,15 +1279,14 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
 }
 
 template <int LAYOUT, bool EVEN, int NB = 1, int XPER = 2, bool ROT = false, int PRO = 0,
-          bool PHASE = false, bool MX = false>
+          bool PHASE = false>
 __global__ __launch_bounds__(kMaxWaves * 64) void gemv_kernel(GemvArgs a) {
-  gemv_body<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE, MX>(a);
+  gemv_body<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE, false>(a);
 }
 
-// Matrix-core batches of 2 and 4 activations: held to 128 registers (four
-// waves per SIMD), so that two 8-wave workgroups share a CU when there are
-// more tiles than CUs.  Wider batches would spill there, and their staged
-// activations mostly leave LDS for one workgroup a CU anyway.
+// Matrix-core batches of 2 and 4 activations (wider ones: batch.hip): held to
+// 128 registers (four waves per SIMD), so that two 8-wave workgroups share a CU
+// when there are more tiles than CUs.
 template <int LAYOUT, bool EVEN, int NB, int XPER>
 __global__ __launch_bounds__(kMaxWaves * 64, 4) void gemv_kernel_mx(GemvArgs a) {
   gemv_body<LAYOUT, EVEN, NB, XPER, false, 0, false, true>(a);
@@ -1580,21 +1454,20 @@ static size_t gemv_lds_bytes(const GemvArgs& a) {
 template <int LAYOUT, bool EVEN, int NB, int XPER, bool ROT = false, int PRO = 0,
           bool PHASE = false, bool MX = false>
 static int launch_gemv_kernel(const GemvArgs& a, size_t shmem, hipStream_t st) {
-  constexpr bool kCapped = MX && NB <= 4;
   const void* fn;
-  if constexpr (kCapped)
+  if constexpr (MX)
     fn = (const void*)gemv_kernel_mx<LAYOUT, EVEN, NB, XPER>;
   else
-    fn = (const void*)gemv_kernel<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE, MX>;
+    fn = (const void*)gemv_kernel<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE>;
   if (shmem > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     if (e != hipSuccess) return hip_fail("hipFuncSetAttribute", e);
   }
-  if constexpr (kCapped)
+  if constexpr (MX)
     hipLaunchKernelGGL((gemv_kernel_mx<LAYOUT, EVEN, NB, XPER>), dim3((unsigned)a.tiles),
                        dim3(64 * a.waves), shmem, st, a);
   else
-    hipLaunchKernelGGL((gemv_kernel<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE, MX>),
+    hipLaunchKernelGGL((gemv_kernel<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE>),
                        dim3((unsigned)a.tiles), dim3(64 * a.waves), shmem, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail("gemv launch", e);
@@ -1636,7 +1509,6 @@ static int launch_gemv_as(const GemvArgs& a, size_t shmem, hipStream_t st) {
   return launch_gemv_pro<LAYOUT, EVEN, NB, 2, PHASE, MX>(a, shmem, st);
 }
 
-
 template <int LAYOUT, int NB = 1, bool PHASE = false, bool MX = false>
 static int launch_gemv(const GemvArgs& a0, hipStream_t st) {
   GemvArgs a = a0;
@@ -1675,14 +1547,12 @@ static int launch_gemv_rotated(const GemvArgs& a, hipStream_t st) {
   return launch_gemv_kernel<LEECH_PLANES14, false, 1, 1, true>(a, shmem, st);
 }
 
-// Batch width of the next chunk of a batched launch: 2, 4, 8 or 16 (the next
+// Batch width of the next chunk of a v_dot2 batch: 2, 4, 8 or 16 (the next
 // power of two at or above the vectors left, at most 16; vectors past the
 // chunk's count read zero), narrowed until the activations fit in LDS; 1 for
-// a single vector left on the dot-product path, or when not even two fit.  On
-// the matrix-core path a single vector left still runs 2 wide, so that every
-// vector of a batch gets the same arithmetic.
-static int batch_width(const GemvArgs& a, int left, bool mx) {
-  if (left <= 1 && !mx) return 1;
+// a single vector left, or when not even two fit.
+static int batch_width(const GemvArgs& a, int left) {
+  if (left <= 1) return 1;
   for (int w = left > 8 ? 16 : left > 4 ? 8 : left > 2 ? 4 : 2; w >= 2; w >>= 1) {
     const size_t need = w == 16  ? gemv_lds_bytes<LEECH_PLANES14, 16>(a)
                         : w == 8 ? gemv_lds_bytes<LEECH_PLANES14, 8>(a)
@@ -1693,14 +1563,25 @@ static int batch_width(const GemvArgs& a, int left, bool mx) {
   return 1;
 }
 
-// Products of batched launches: the 16-block 4×4×4 MFMA form (default) or
-// v_dot2 per activation.
+// Products of batched launches: the matrix cores (default) or v_dot2 per
+// activation.
 static std::atomic<int> g_batch_mode{LEECH_BATCH_AUTO};
 
-template <int NB>
-static int launch_batch(const GemvArgs& c, bool mx, hipStream_t st) {
-  return mx ? launch_gemv<LEECH_PLANES14, NB, false, true>(c, st)
-            : launch_gemv<LEECH_PLANES14, NB>(c, st);
+// A matrix-core batch: up to four activations that fit in LDS beside the class
+// table in one gemv_kernel_mx launch, whose steps read whole units and have no
+// idle activation rows; everything else through batch.hip's kernel.  (Both
+// give the same bits.)
+static int launch_batch_mx(const GemvArgs& a, hipStream_t st) {
+  if (a.nbatch <= 2 && gemv_lds_bytes<LEECH_PLANES14, 2>(a) <= 160 * 1024)
+    return launch_gemv<LEECH_PLANES14, 2, false, true>(a, st);
+  if (a.nbatch <= 4 && gemv_lds_bytes<LEECH_PLANES14, 4>(a) <= 160 * 1024)
+    return launch_gemv<LEECH_PLANES14, 4, false, true>(a, st);
+  // the activation lengths that the single GEMV serves
+  if (gemv_lds_bytes<LEECH_PLANES14>(a) > 160 * 1024)
+    return set_error(LEECH_E_SHAPE, "Kpad too large for the LDS-staged activation");
+  const BatchCall c = {a.main, a.table, a.scale, a.x,   a.y,   a.cen0, a.cen1, a.main_bytes,
+                       a.M,    a.nb,    a.ldx,   a.ldy, a.C, a.R,    a.nbatch};
+  return launch_batch_mfma(c, st);
 }
 
 template <int LAYOUT>
@@ -1793,17 +1674,20 @@ int leech_gemv_batch(const leech_layout_desc* desc, const void* d_main, const vo
   a.ldx = ldx;
   a.ldy = ldy;
   const hipStream_t st = (hipStream_t)stream;
-  const bool mx = batch > 1 && g_batch_mode.load(std::memory_order_relaxed) == LEECH_BATCH_AUTO;
+  if (batch > 1 && g_batch_mode.load(std::memory_order_relaxed) == LEECH_BATCH_AUTO) {
+    a.nbatch = batch;
+    return launch_batch_mx(a, st);
+  }
   for (int b0 = 0; b0 < batch;) {
-    const int w = batch_width(a, batch - b0, mx);
+    const int w = batch_width(a, batch - b0);
     GemvArgs c = a;
     c.x = d_X + (int64_t)b0 * ldx;
     c.y = d_Y + (int64_t)b0 * ldy;
     c.nbatch = std::min(w, batch - b0);
-    rc = w == 16  ? launch_batch<16>(c, mx, st)
-         : w == 8 ? launch_batch<8>(c, mx, st)
-         : w == 4 ? launch_batch<4>(c, mx, st)
-         : w == 2 ? launch_batch<2>(c, mx, st)
+    rc = w == 16  ? launch_gemv<LEECH_PLANES14, 16>(c, st)
+         : w == 8 ? launch_gemv<LEECH_PLANES14, 8>(c, st)
+         : w == 4 ? launch_gemv<LEECH_PLANES14, 4>(c, st)
+         : w == 2 ? launch_gemv<LEECH_PLANES14, 2>(c, st)
                   : gemv_dispatch(desc, c, st);
     if (rc) return rc;
     b0 += c.nbatch;

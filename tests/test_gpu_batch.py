@@ -173,6 +173,37 @@ def test_matrix_core_bits_independent_of_batch(dev, dcb, geo, M, K):
         assert np.array_equal(Y.view(np.uint32), np.roll(full, shift, 0).view(np.uint32)), shift
 
 
+# the wide kernel's tiles of every lane_cols (by the batch, which sets the
+# number of workgroups), with ragged tiles, row blocks and last column groups
+TILE_CASES = [((1, 64), 333, 24 * 21, 1700), ((1, 64), 333, 24 * 21, 850), ((1, 48), 333, 24 * 9, 424),
+              ((1, 64), 70, 24 * 3, 5), ((2, 32), 333, 24 * 23, 856), ((2, 28), 100, 24 * 17, 1300),
+              ((2, 24), 100, 24 * 40, 9), ((3, 20), 333, 24 * 50, 860), ((3, 12), 70, 24 * 26, 1701),
+              ((3, 20), 70, 24 * 49, 17), ((4, 16), 333, 24 * 39, 857), ((4, 16), 100, 24 * 33, 1281),
+              ((4, 4), 333, 24 * 5, 240), ((4, 12), 17, 24 * 70, 33), ((8, 8), 333, 24 * 67, 465),
+              ((8, 4), 100, 24 * 41, 641), ((8, 8), 9, 24 * 9, 6), ((16, 4), 333, 24 * 131, 240),
+              ((16, 4), 30, 24 * 18, 19)]
+
+
+@pytest.mark.parametrize("geo,M,K,B", TILE_CASES)
+def test_wide_batch_tiles(dev, dcb, geo, M, K, B):
+    """Every tile of the wide kernel, strided activations and outputs: the bits
+    of the four-activation launches (which the tests above hold to the oracle
+    and the single GEMV)."""
+    say(f"[batch tiles] {geo} {M}x{K} B={B}")
+    inp, mat = build(dev, dcb, M, K, M + B, geometry=geo)
+    g = torch.Generator().manual_seed(B)
+    X = torch.randn(B, inp.Kpad + 8, generator=g).half().to(dev)
+    Y = torch.full((B, M + 1), -3.0, dtype=torch.float32, device=dev)
+    mat.gemv_batch(X[:, :inp.Kpad], Y[:, :M], centroids=CEN)
+    ref = torch.empty((B, M), dtype=torch.float32, device=dev)
+    for b in range(0, B, 4):
+        n = min(4, B - b)
+        x = X[b:b + n, :inp.Kpad] if n > 1 else X[b - 1:b + 1, :inp.Kpad]
+        ref[b:b + n] = mat.gemv_batch(x, centroids=CEN)[-n:]
+    assert torch.equal(Y[:, :M].view(torch.int32), ref.view(torch.int32))
+    assert torch.all(Y[:, M] == -3.0)
+
+
 def test_batch_mode_rejects_unknown(dev):
     with pytest.raises(P.LeechError):
         P.set_batch_mode(7)
