@@ -107,6 +107,57 @@ def test_invalid_codes_are_counted_and_zeroed(dev, dcb):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("M,nb,geo", [(1, 1, (1, 4)), (1, 1, (16, 4)), (5, 3, (2, 32)), (63, 5, (3, 20)),
+                                      (65, 2, (1, 64)), (4, 67, (8, 8)), (130, 19, (4, 16)),
+                                      (37, 33, (16, 4)), (9, 4, (1, 4))])
+def test_transcode_geometries(dev, dcb, M, nb, geo):
+    """Runs of 64 slots that cross tiles and units, ragged last tiles and
+    groups, units of one block: every slot's record is its block's."""
+    say(f"[transcode] geometry {geo} {M}x{nb}")
+    inp = synth.make_gemv_inputs(M, 24 * nb, seed=M + nb, name="transcode-geo")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z)
+    codes = P.index_encode(dcb.cb, cls, inp.gain, sm, lv)
+    desc, main, _, _ = P.expand_layout(dcb.cb, P.PLANES14, cls, inp.gain, sm, lv, geo)
+    d_codes = torch.from_numpy(codes.view(np.int64)).to(dev)
+    got = torch.full((desc.main_bytes,), 0xAB, dtype=torch.uint8, device=dev)
+    bad = torch.full((1,), 77, dtype=torch.int32, device=dev)
+    _lib.transcode_planes14(desc, dcb.index.data_ptr(), d_codes.data_ptr(), got.data_ptr(),
+                            bad.data_ptr())
+    assert int(bad.item()) == 0
+    assert np.array_equal(got.cpu().numpy(), main)
+
+
+def test_transcode_tile_past_32_bits(dev, dcb):
+    """One row of 2^29 + 3 blocks in tiles of 4: a tile of more than 2^31 slots
+    takes the 64-bit slot arithmetic.  With one row the stream is in block
+    order, so it must be the records of the repeated pool of codes."""
+    nb, pool = (1 << 29) + 3, 4099
+    if torch.cuda.mem_get_info(dev)[0] < 24 << 30:
+        pytest.skip("needs 24 GB of device memory")
+    say("[transcode] one row past 32-bit tiles")
+    inp = synth.make_gemv_inputs(1, 24 * pool, seed=3, name="transcode-long")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z)
+    codes = torch.from_numpy(P.index_encode(dcb.cb, cls, inp.gain, sm, lv).view(np.int64)).to(dev)
+    _, main, _, _ = P.expand_layout(dcb.cb, P.PLANES14, cls, inp.gain, sm, lv, (16, 4))
+    recs = torch.from_numpy(main[:14 * pool].reshape(pool, 14)).to(dev)
+    desc = P.planes14_desc(1, 24 * nb, (16, 4))
+    reps = -(-nb // pool)
+    d_codes = codes.reshape(-1).repeat(reps)[:nb].contiguous()
+    got = torch.empty(desc.main_bytes, dtype=torch.uint8, device=dev)
+    bad = torch.full((1,), 77, dtype=torch.int32, device=dev)
+    _lib.transcode_planes14(desc, dcb.index.data_ptr(), d_codes.data_ptr(), got.data_ptr(),
+                            bad.data_ptr())
+    assert int(bad.item()) == 0
+    whole = nb // pool
+    body = got[:14 * pool * whole].view(whole, pool, 14)
+    for i in range(0, whole, 8192):
+        assert bool((body[i:i + 8192] == recs).all())
+    rest = nb - whole * pool
+    tail = got[14 * pool * whole:]
+    assert torch.equal(tail[:14 * rest].view(rest, 14), recs[:rest])
+    assert bool((tail[14 * rest:] == 0).all())
+
+
 def host_storage_index(desc):
     """Storage slot of block (r, j) in the wave-tile order (rows grouped in
     tiles of tile_rows, units of lane_cols columns, stored row by row)."""
