@@ -457,6 +457,14 @@ int leech_noweights_ctrl(const leech_layout_desc* desc, const uint16_t* d_x, flo
 int leech_rotate_x(int64_t K, int64_t Kpad, const uint16_t* d_x, const int8_t* d_signs,
                    uint16_t* d_xr, float* d_xr32, void* stream);
 
+/* leech_layout_scales on the device: permutes per-block fp16 scales from
+ * row-major (r, j) order into the descriptor's wave-tile order, both device
+ * arrays of M·nb binary16 values that do not overlap.  Asynchronous on `stream`.
+ * LEECH_E_ARG for a NULL or misaligned pointer, LEECH_E_SHAPE for a descriptor
+ * that is not valid. */
+int leech_layout_scales_device(const leech_layout_desc* desc, const uint16_t* d_scale_rowmajor,
+                               uint16_t* d_scale_out, void* stream);
+
 /* Load-time transcoder on the device (§2.2: each block's index is expanded
  * once into its decoded-field record): format-v1 codes -> the Planes14 main
  * stream, bit-identical to leech_expand_layout's.  desc: a Planes14

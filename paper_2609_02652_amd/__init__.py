@@ -91,12 +91,19 @@ class LeechMatrix:
         bad = torch.empty(1, dtype=torch.int32, device=dev)
         _lib.transcode_planes14(desc, dcb.index.data_ptr(), codes.data_ptr(), main.data_ptr(),
                                 bad.data_ptr(), _stream(stream))
+        # the scales take their storage order on the device; on the current
+        # stream, like the copy, so that the wait below covers them
+        rowmajor = np.ascontiguousarray(scale_rowmajor, np.float16).reshape(-1)[: M * nb]
+        if rowmajor.size < M * nb:
+            raise ValueError("scale_rowmajor must hold one fp16 scale per block")
+        rows = _dev(rowmajor, dev)
+        scale = torch.empty_like(rows)
+        _lib.layout_scales_device(desc, rows.data_ptr(), scale.data_ptr(), _stream(None))
         n_bad = int(bad.item())
         if n_bad:
             raise LeechError(-4, f"{n_bad} of {M * nb} block codes are not format-v1 codes")
-        sc = layout_scales(desc, scale_rowmajor)
         empty = torch.empty(0, dtype=torch.uint8, device=dev)
-        return cls(desc, main, empty, empty, _dev(sc, dev), dcb)
+        return cls(desc, main, empty, empty, scale, dcb)
 
     @property
     def M(self):

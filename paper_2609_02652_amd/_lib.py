@@ -25,7 +25,7 @@ ERRORS = {0: "OK", -1: "LEECH_E_ARG", -2: "LEECH_E_LAYOUT", -3: "LEECH_E_SHAPE",
 EXPORTS = ["leech_last_error", "leech_codebook_build", "leech_codebook_free",
            "leech_codebook_info", "leech_codebook_class", "leech_codebook_table",
            "leech_fields_from_points", "leech_expand_layout", "leech_layout_scales",
-           "leech_host_decode_layout", "leech_gemv", "leech_gemv_grouped", "leech_decode_blocks",
+           "leech_layout_scales_device", "leech_host_decode_layout", "leech_gemv", "leech_gemv_grouped", "leech_decode_blocks",
            "leech_fp16_gemv_ref", "leech_noweights_ctrl", "leech_rotate_x",
            "leech_index_encode", "leech_index_decode", "leech_planes14_desc",
            "leech_transcode_planes14", "leech_set_exception_mode", "leech_gemv_batch",
@@ -93,6 +93,7 @@ def _load() -> C.CDLL:
         "leech_index_encode": (I, [P, I64, P, P, P, P, P]),
         "leech_index_decode": (I, [P, I64, P, P, P, P, P]),
         "leech_planes14_desc": (I, [I64, I64, I32, I32, C.POINTER(LayoutDesc)]),
+        "leech_layout_scales_device": (I, [C.POINTER(LayoutDesc), P, P, P]),
         "leech_transcode_planes14": (I, [C.POINTER(LayoutDesc), P, P, P, P, P]),
         "leech_set_exception_mode": (I, [I]),
         "leech_set_prologue_mode": (I, [I]),
@@ -332,6 +333,10 @@ def noweights_ctrl(desc, d_x, d_y, stream=0):
 
 def rotate_x(K, Kpad, d_x, d_signs, d_xr, d_xr32=0, stream=0):
     check(lib.leech_rotate_x(K, Kpad, d_x, d_signs or None, d_xr, d_xr32 or None, stream or None))
+
+
+def layout_scales_device(desc, d_rowmajor, d_out, stream=0):
+    check(lib.leech_layout_scales_device(C.byref(desc), d_rowmajor, d_out, stream or None))
 
 
 def transcode_planes14(desc, d_index_table, d_code, d_main, d_bad, stream=0):

@@ -358,6 +358,18 @@ __global__ __launch_bounds__(kTcThreads) void transcode_planes14_kernel(Transcod
 
 __global__ void clear_u32_kernel(uint32_t* p) { *p = 0; }
 
+// The block scales in storage order: a thread a slot, so the writes are
+// contiguous and the reads gather; bound by its launch (11 MB of scales and less
+// in real matrices).
+__global__ __launch_bounds__(256) void scale_order_kernel(TranscodeArgs a,
+                                                          const uint16_t* __restrict__ in,
+                                                          uint16_t* __restrict__ out) {
+  const uint64_t s0 = (uint64_t)blockIdx.x * 256;
+  const uint64_t t0 = s0 / a.tile_blocks;
+  for (int k = threadIdx.x; k < 256 && s0 + k < a.n; k += blockDim.x)
+    out[s0 + k] = in[block_of_slot(a, t0, s0 - t0 * a.tile_blocks, k)];
+}
+
 int tc_fail(const char* what, hipError_t e) {
   return set_error(LEECH_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -365,33 +377,12 @@ int tc_fail(const char* what, hipError_t e) {
 }  // namespace
 }  // namespace leech
 
-using namespace leech;
-
-extern "C" int leech_transcode_planes14(const leech_layout_desc* desc, const void* d_index_table,
-                                        const uint64_t* d_code, void* d_main, uint32_t* d_bad,
-                                        void* stream) {
-  clear_error();
-  if (!desc || !d_index_table || !d_code || !d_main || !d_bad)
-    return set_error(LEECH_E_ARG, "NULL argument");
-  if (desc->layout != LEECH_PLANES14)
-    return set_error(LEECH_E_LAYOUT, "the transcoder writes the Planes14 layout only");
-  if (desc->M <= 0 || desc->Kpad <= 0 || desc->Kpad % kDim || desc->nb != desc->Kpad / kDim ||
-      !geometry_ok(desc->lane_cols, desc->tile_rows))
-    return set_error(LEECH_E_SHAPE, "descriptor shape is not valid");
-  const int64_t n = desc->M * desc->nb;
-  if (desc->main_bytes != (uint64_t)n * kPlanes14Bytes + kPadBytes)
-    return set_error(LEECH_E_SHAPE, "descriptor size is not the Planes14 size of its shape");
-  if (((uintptr_t)d_main & 15) || ((uintptr_t)d_code & 7) || ((uintptr_t)d_index_table & 15))
-    return set_error(LEECH_E_ARG, "misaligned device pointer");
-  Geometry geo(desc->M, desc->nb, desc->lane_cols, desc->tile_rows);
-  TranscodeArgs a;
-  a.T = (const IdxTable*)d_index_table;
-  a.code = d_code;
-  a.main = (uint8_t*)d_main;
-  a.bad = d_bad;
-  a.main_bytes = desc->main_bytes;
-  a.runs = (desc->main_bytes + kRunBytes - 1) / kRunBytes;
-  a.n = (uint64_t)n;
+namespace leech {
+namespace {
+// The slot arithmetic of a matrix in a geometry.
+TranscodeArgs slot_args(const Geometry& geo) {
+  TranscodeArgs a = {};
+  a.n = (uint64_t)geo.M * (uint64_t)geo.nb;
   a.tile_blocks = (uint64_t)geo.R * (uint64_t)geo.nb;
   a.M = (uint64_t)geo.M;
   a.nb = (uint64_t)geo.nb;
@@ -405,6 +396,61 @@ extern "C" int leech_transcode_planes14(const leech_layout_desc* desc, const voi
   a.inv_tile = reciprocal(a.tile_blocks);
   a.inv_unit = reciprocal((uint64_t)a.R * a.C);
   a.inv_unit_last = reciprocal((uint64_t)a.rows_last * a.C);
+  return a;
+}
+int check_geometry(const leech_layout_desc* desc) {
+  if (desc->M <= 0 || desc->Kpad <= 0 || desc->Kpad % kDim || desc->nb != desc->Kpad / kDim ||
+      !geometry_ok(desc->lane_cols, desc->tile_rows))
+    return set_error(LEECH_E_SHAPE, "descriptor shape is not valid");
+  return LEECH_OK;
+}
+}  // namespace
+}  // namespace leech
+
+using namespace leech;
+
+extern "C" int leech_layout_scales_device(const leech_layout_desc* desc,
+                                          const uint16_t* d_scale_rowmajor, uint16_t* d_scale_out,
+                                          void* stream) {
+  clear_error();
+  if (!desc || !d_scale_rowmajor || !d_scale_out) return set_error(LEECH_E_ARG, "NULL argument");
+  int rc = check_geometry(desc);
+  if (rc) return rc;
+  if (((uintptr_t)d_scale_rowmajor & 1) || ((uintptr_t)d_scale_out & 1))
+    return set_error(LEECH_E_ARG, "misaligned device pointer");
+  const TranscodeArgs a =
+      slot_args(Geometry(desc->M, desc->nb, desc->lane_cols, desc->tile_rows));
+  const uint64_t blocks = (a.n + 255) / 256;
+  if (blocks > 0x7fffffff) return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
+  hipLaunchKernelGGL(scale_order_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream,
+                     a, d_scale_rowmajor, d_scale_out);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return tc_fail("scale order launch", e);
+  return LEECH_OK;
+}
+
+extern "C" int leech_transcode_planes14(const leech_layout_desc* desc, const void* d_index_table,
+                                        const uint64_t* d_code, void* d_main, uint32_t* d_bad,
+                                        void* stream) {
+  clear_error();
+  if (!desc || !d_index_table || !d_code || !d_main || !d_bad)
+    return set_error(LEECH_E_ARG, "NULL argument");
+  if (desc->layout != LEECH_PLANES14)
+    return set_error(LEECH_E_LAYOUT, "the transcoder writes the Planes14 layout only");
+  int rc = check_geometry(desc);
+  if (rc) return rc;
+  const int64_t n = desc->M * desc->nb;
+  if (desc->main_bytes != (uint64_t)n * kPlanes14Bytes + kPadBytes)
+    return set_error(LEECH_E_SHAPE, "descriptor size is not the Planes14 size of its shape");
+  if (((uintptr_t)d_main & 15) || ((uintptr_t)d_code & 7) || ((uintptr_t)d_index_table & 15))
+    return set_error(LEECH_E_ARG, "misaligned device pointer");
+  TranscodeArgs a = slot_args(Geometry(desc->M, desc->nb, desc->lane_cols, desc->tile_rows));
+  a.T = (const IdxTable*)d_index_table;
+  a.code = d_code;
+  a.main = (uint8_t*)d_main;
+  a.bad = d_bad;
+  a.main_bytes = desc->main_bytes;
+  a.runs = (desc->main_bytes + kRunBytes - 1) / kRunBytes;
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) == hipSuccess)
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);

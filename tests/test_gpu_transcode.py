@@ -125,6 +125,12 @@ def test_transcode_geometries(dev, dcb, M, nb, geo):
                             bad.data_ptr())
     assert int(bad.item()) == 0
     assert np.array_equal(got.cpu().numpy(), main)
+    # the scales' order on the device is the host's
+    rows = torch.from_numpy(inp.scale.reshape(-1).view(np.int16)).to(dev)
+    order = torch.zeros(M * nb + 1, dtype=torch.int16, device=dev)
+    _lib.layout_scales_device(desc, rows.data_ptr(), order.data_ptr())
+    want = P.layout_scales(desc, inp.scale).view(np.int16)
+    assert np.array_equal(order.cpu().numpy(), np.append(want, np.int16(0)))
 
 
 def test_transcode_tile_past_32_bits(dev, dcb):
