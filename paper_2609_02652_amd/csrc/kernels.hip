@@ -160,9 +160,18 @@ struct LdsSide {
   }
 };
 
-// Golay70 in LDS: the generator table, and each class's Planes14 table (for
-// an exception's exact record)
-constexpr int kG70LdsBytes = 128 * 4 + 512 * 8;
+// Golay70 in LDS: the generator table at byte 0, before the class table, so
+// that a message's fields are its words' addresses, and after x each class's
+// Planes14 table (for an exception's exact record)
+constexpr int kG70GenBytes = 128 * 4;
+constexpr int kG70LdsBytes = kG70GenBytes + 512 * 8;
+
+// A load at a byte address of the dynamic LDS, which starts at 0 in kernels
+// without static LDS: through a generic pointer the compiler adds the base.
+template <class T>
+__device__ __forceinline__ T lds_at(uint32_t byte) {
+  return *(const __attribute__((address_space(3))) T*)(uintptr_t)byte;
+}
 
 // (m & a) | (~m & b) as one v_bfi_b32: left to itself the compiler splits the
 // nibble transpose's bit-field inserts into and / and_or pairs.
@@ -805,8 +814,10 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
   constexpr bool kRamp = kFirstUnits < kPrefetch;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr bool kW = LAYOUT != kNoWeights;
-  LdsEntry* ts = (LdsEntry*)smem;                    // one table copy, or two
-  uint8_t* const xbase = smem + (kW ? (a.tab2 ? 2 : 1) * a.tab_bytes : 0);
+  constexpr uint32_t kTab0 = LAYOUT == LEECH_GOLAY70 ? kG70GenBytes : 0;
+  LdsEntry* ts = (LdsEntry*)(smem + kTab0);          // one table copy, or two
+  LdsEntry* ts2 = (LdsEntry*)(smem + kTab0 + a.tab_bytes);
+  uint8_t* const xbase = smem + kTab0 + (kW ? (a.tab2 ? 2 : 1) * a.tab_bytes : 0);
   constexpr bool kUnits = has_units<LAYOUT>();
   constexpr bool kExc = has_exc<LAYOUT>();
   const int64_t nb = a.nb;
@@ -814,9 +825,8 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
   const int xblocks = groups * C;
   uint32_t* xs = (uint32_t*)xbase;                                 // NB × xblocks × 12 x pairs
   uint8_t* p = xbase + (size_t)NB * xblocks * 48;
-  uint32_t* cws = (uint32_t*)p;                                    // Golay70: 128 words
-  u32x2a* p14t = (u32x2a*)(p + 128 * 4);                           // Golay70: 512 tables
-  if constexpr (LAYOUT == LEECH_GOLAY70) p += kG70LdsBytes;
+  u32x2a* p14t = (u32x2a*)p;                                       // Golay70: 512 tables
+  if constexpr (LAYOUT == LEECH_GOLAY70) p += kG70LdsBytes - kG70GenBytes;
   uint8_t* units_lds = p;                                          // groups × 16 B
   if constexpr (kUnits) p += (size_t)groups * kUnitEntryBytes;
   const bool red_x = red_in_x(NB, xblocks, waves);
@@ -934,15 +944,14 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
       cen1b = a.grp_cen[gi + 1][1];
     }
   }
-  const uint32_t toff = two && rl >= split ? a.tab_bytes : 0u;
+  const uint32_t toff = kTab0 + (two && rl >= split ? a.tab_bytes : 0u);
   if constexpr (kW)
     for (int c = tid + nthr; c < kBallClasses; c += nthr) {
       ts[c] = make_entry_as<LAYOUT>(a.table, (uint32_t)c, cen0, cen1);
       ts[c + 512] = make_entry_as<LAYOUT>(a.table, (uint32_t)c | 512u, cen0, cen1);
       if (two) {
-        LdsEntry* t2 = (LdsEntry*)(smem + a.tab_bytes);
-        t2[c] = make_entry_as<LAYOUT>(a.table, (uint32_t)c, cen0b, cen1b);
-        t2[c + 512] = make_entry_as<LAYOUT>(a.table, (uint32_t)c | 512u, cen0b, cen1b);
+        ts2[c] = make_entry_as<LAYOUT>(a.table, (uint32_t)c, cen0b, cen1b);
+        ts2[c + 512] = make_entry_as<LAYOUT>(a.table, (uint32_t)c | 512u, cen0b, cen1b);
       }
       if constexpr (LAYOUT == LEECH_GOLAY70) p14t[c] = *(const u32x2a*)&a.table[c];
     }
@@ -1061,18 +1070,18 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
       e.factor = f * cen1;
       ts[tid + 512] = e;
       if (two) {
-        LdsEntry* t2 = (LdsEntry*)(smem + a.tab_bytes);
         e.factor = f * cen0b;
-        t2[tid] = e;
+        ts2[tid] = e;
         e.factor = f * cen1b;
-        t2[tid + 512] = e;
+        ts2[tid + 512] = e;
       }
     }
     if constexpr (LAYOUT == LEECH_GOLAY70)
       if (tid < 32) {
         // the codeword is a xor of two words: placing those places it
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cws[4 * tid + q] = g70_place(gr[q], (uint32_t)gr[q] >> 4);
+        for (int q = 0; q < 4; ++q)
+          ((uint32_t*)smem)[4 * tid + q] = g70_place(gr[q], (uint32_t)gr[q] >> 4);
       }
   }
   if constexpr (kUnits) {
@@ -1089,6 +1098,13 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
   // the second at toff), in the layout's arrangement and as a Planes14 table,
   // and the entry at a table byte address
   auto tab_at = [&](uint32_t addr) -> LdsEntry {
+    // one 16-byte read and no base to add: 17408×5120 Golay70 18.8 -> 18.3 µs,
+    // 28672×4096 rotated 17.4 -> 17.1, four activations 16.8 -> 16.6; the
+    // plain Planes14 launch is slower with it (16384² 30.0 -> 30.6 µs)
+    if constexpr (LAYOUT == LEECH_GOLAY70 || ROT || MX) {
+      const u32x4a v = lds_at<u32x4a>(addr);
+      return LdsEntry{v.x, v.y, __builtin_bit_cast(float, (uint32_t)v.z), v.w};
+    }
     return *(const LdsEntry*)__builtin_assume_aligned(smem + addr, 16);
   };
   auto tab = [&](uint32_t e16) -> LdsEntry {
@@ -1108,7 +1124,9 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
     return t;
   };
   auto tab14 = [&](uint32_t e16) -> LdsEntry { return as14(e16, toff); };
-  auto cw = [&](uint32_t m) -> uint32_t { return golay_word(cws, m); };
+  auto cw = [&](uint32_t m) -> uint32_t {
+    return lds_at<uint32_t>(4 * (m & 63u)) ^ lds_at<uint32_t>(4 * (m >> 6) + 256);
+  };
 
   // Hoisted exception decoder (Planes12x, Golay70): each of the tile's
   // exceptions is decoded once, densely, before the loop, into a table entry
@@ -1135,7 +1153,7 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
         for (int k = 0; k < 12; ++k) xw[k] = xj[k];
         uint32_t e16, W[3], h[12];
         p14_record(w.x, w.y, w.z, w.w, 0u, 28u, W, e16);
-        const uint32_t off = two && (int)(ul / cols) >= split ? a.tab_bytes : 0u;
+        const uint32_t off = kTab0 + (two && (int)(ul / cols) >= split ? a.tab_bytes : 0u);
         const LdsEntry te = as14(e16, off);
         p14_core(W, te.tlo, te.thi, h);
         LdsEntry k;
