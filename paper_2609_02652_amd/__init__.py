@@ -34,7 +34,9 @@ def _torch():
 def _stream(stream):
     torch = _torch()
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the current stream's handle itself: a Stream object built only to be
+        # read was 2.9 µs of a call's 9 on the host
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
