@@ -1344,39 +1344,36 @@ __global__ __launch_bounds__(kMaxWaves * 64, 4) void gemv_kernel_mx(GemvArgs a) 
 }
 
 // --------------------------------------------------------- decode export
-// One thread per block, with the GEMV's decode function and plain loads at
-// the block's own byte offset; the binary16 pairs are turned back into integer
-// coordinates (|z| in the low byte of each half, the sign in its bit 15).
+// Verification decode with the GEMV's decode function and plain loads.  A
+// workgroup takes eight consecutive units of a tile, a wave one unit at a time
+// in storage order, so records are read once and in line and a lane's place
+// needs no division by the matrix's shape.  The binary16 pairs become integer
+// coordinates (|z| in the low byte of each half, the sign in its bit 15),
+// which pass through LDS so that rows leave in runs of 192 bytes and more.
+// Bound by its bytes, 14 read and 27 written a Planes14 block.  A thread a row-major block,
+// with 64-bit divisions and records fetched again for every row that shares
+// their line, took 49.7 µs at 14336×4096 (28.0 now, 3.6 TB/s), 16.4 at
+// 5120×5120 (12.8) and 10.0 at 4096×4096 (9.5); 16 units a workgroup gain at
+// the first (24.9) and lose at 17408×1024 (11.6 against 11.1).
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+constexpr int kDecodeUnits = 8;             // units of a workgroup
+constexpr int kDecodePad = 8;               // bytes after each row's run, against bank conflicts
+
 template <int LAYOUT>
-__global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, int8_t* zout, uint16_t* cout,
-                                                     uint8_t* gout) {
-  const int64_t bi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (bi >= a.M * a.nb) return;
-  const int64_t r = bi / a.nb, j = bi % a.nb;
-  const int tile = (int)(r / a.R);
-  const int g = (int)(j / a.C);
+__global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t chunks, int8_t* zout,
+                                                     uint16_t* cout, uint8_t* gout) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int W = kDecodeUnits * a.C;
+  const int row_bytes = W * kDim + kDecodePad;
+  uint8_t* const zs = smem;
+  uint16_t* const es = (uint16_t*)(smem + a.R * row_bytes);
+  const int tile = (int)(blockIdx.x / chunks);
+  const int g0 = (int)(blockIdx.x % chunks) * kDecodeUnits;
+  const int groups = (int)a.groups;
   const int R_t = (int)min((int64_t)a.R, a.M - (int64_t)tile * a.R);
-  const int C_g = (int)min((int64_t)a.C, a.nb - (int64_t)g * a.C);
-  const uint32_t ul = (uint32_t)((r % a.R) * C_g + (j % a.C));
-  const uint64_t blk = (uint64_t)tile * a.R * a.nb + (uint64_t)g * R_t * a.C + ul;
+  const int C_last = (int)(a.nb - (int64_t)(groups - 1) * a.C);
+  const int lane = threadIdx.x & 63;
   const GlobalSide side{&a};
-  Pref p = {0, 0, 0, 0, 0, 0, 0, 0};
-  if constexpr (LAYOUT == LEECH_SLOT32) {
-    uint64_t bits;
-    uint32_t base;
-    side.unit_entry(a.side0, tile * (int)a.groups + g, bits, base);
-    const uint32_t nbelow = (uint32_t)__builtin_popcountll(bits & ((1ull << ul) - 1ull));
-    const uint32_t* rec = (const uint32_t*)(a.main + (uint64_t)base * 4) +
-                          (ul * (uint32_t)kSlot32Small + nbelow * (uint32_t)(kSlot32Large - kSlot32Small)) / 4;
-    p.w0 = rec[0]; p.w1 = rec[1]; p.w2 = rec[2]; p.w3 = rec[3]; p.w4 = rec[4];
-  } else {
-    const uint64_t off = blk * Stride<LAYOUT>::v;
-    const uint32_t* w = (const uint32_t*)(a.main + (off & ~3ull));
-    p.w0 = w[0]; p.w1 = w[1]; p.w2 = w[2];
-    if constexpr (LAYOUT == LEECH_PLANES14) p.w3 = w[3];
-    p.sh = (uint32_t)(off & 3u) * 8u;
-    p.esh = (p.sh + 28u) & 31u;
-  }
   auto tab = [&](uint32_t e16) -> LdsEntry {
     return make_entry_as<LAYOUT>(a.table, e16 >> 4, 1.0f, 1.0f);
   };
@@ -1385,28 +1382,89 @@ __global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, int8_t* zout, u
     const uint32_t s = golay_word(a.codewords, m);
     return g70_place(s, s >> 4);
   };
-  uint32_t h[12], e16;
-  LdsEntry te;
-  decode_block<LAYOUT>(p, tile, tab, tab14, cw, side, h, e16, te);
-  int8_t z[kDim];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int u = wave; u < kDecodeUnits && g0 + u < groups; u += 4) {
+    const int g = g0 + u;
+    const int C_g = g == groups - 1 ? C_last : a.C;
+    const uint32_t r = (uint32_t)lane * (65536u / (uint32_t)C_g + 1) >> 16;   // lane / C_g
+    const uint32_t col = (uint32_t)(u * a.C) + lane - r * C_g;
+    if (lane >= R_t * C_g) continue;
+    Pref p = {0, 0, 0, 0, 0, 0, 0, 0};
+    if constexpr (LAYOUT == LEECH_SLOT32) {
+      uint64_t bits;
+      uint32_t base;
+      side.unit_entry(a.side0, tile * groups + g, bits, base);
+      const uint32_t nbelow = (uint32_t)__builtin_popcountll(bits & ((1ull << lane) - 1ull));
+      const uint32_t* rec = (const uint32_t*)(a.main + (uint64_t)base * 4) +
+                            (lane * (uint32_t)kSlot32Small +
+                             nbelow * (uint32_t)(kSlot32Large - kSlot32Small)) / 4;
+      const u32x4 w = *(const u32x4*)rec;
+      p.w0 = w.x; p.w1 = w.y; p.w2 = w.z; p.w3 = w.w; p.w4 = rec[4];
+    } else {
+      const uint64_t off =
+          ((uint64_t)tile * a.R * a.nb + (uint64_t)g * (R_t * a.C) + lane) * Stride<LAYOUT>::v;
+      const uint8_t* w = a.main + (off & ~3ull);
+      if constexpr (LAYOUT == LEECH_PLANES14) {
+        const u32x4 v = *(const u32x4*)w;
+        p.w0 = v.x; p.w1 = v.y; p.w2 = v.z; p.w3 = v.w;
+      } else {
+        const u32x3 v = *(const u32x3*)w;
+        p.w0 = v.x; p.w1 = v.y; p.w2 = v.z;
+      }
+      p.sh = (uint32_t)(off & 3u) * 8u;
+      p.esh = (p.sh + 28u) & 31u;
+    }
+    uint32_t h[12], e16;
+    LdsEntry te;
+    decode_block<LAYOUT>(p, tile, tab, tab14, cw, side, h, e16, te);
+    // each half's magnitude, negated where its sign bit is set: a 16-bit
+    // number whose low byte is the coordinate
+    uint32_t v[12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    int c0, c1;
-    pair_coords(k, c0, c1);
-    const int m0 = (int)(h[k] & 0xFFu), m1 = (int)((h[k] >> 16) & 0xFFu);
-    z[c0] = (int8_t)(((h[k] >> 15) & 1u) ? -m0 : m0);
-    z[c1] = (int8_t)(((h[k] >> 31) & 1u) ? -m1 : m1);
+    for (int k = 0; k < 12; ++k) {
+      const s16x2 neg = __builtin_bit_cast(s16x2, h[k]) >> (short)15;
+      v[k] = __builtin_bit_cast(
+          uint32_t, (__builtin_bit_cast(s16x2, h[k] & 0x00FF00FFu) ^ neg) - neg);
+    }
+    // coordinate 4g + r stands in pair 3r + m: g = 0, 1, 2 in low halves (m =
+    // g), 4, 5, 3 in high ones (m = 0, 1, 2)
+    u32x2a* zo = (u32x2a*)(zs + r * row_bytes + col * kDim);
+    uint32_t zw[6];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      const uint32_t lo = perm(v[3 + m], v[m], 0x06020400u);      // rows 0 and 1
+      const uint32_t hi = perm(v[9 + m], v[6 + m], 0x06020400u);  // rows 2 and 3
+      zw[m] = perm(hi, lo, 0x05040100u);
+      zw[m < 2 ? 4 + m : 3] = perm(hi, lo, 0x07060302u);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) zo[q] = u32x2a{zw[2 * q], zw[2 * q + 1]};
+    es[r * W + col] = (uint16_t)(e16 >> 4);
   }
+  __syncthreads();
+  // rows out, the flat index divided by a row's share with a reciprocal that
+  // is exact below 1536 · 384 < 2^20
+  const uint32_t cols = (uint32_t)min((int64_t)W, a.nb - (int64_t)g0 * a.C);
+  const int64_t blk0 = (int64_t)tile * a.R * a.nb + (int64_t)g0 * a.C;
   if (zout) {
-    uint32_t* zo = (uint32_t*)(zout + bi * kDim);
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-      zo[q] = (uint32_t)(uint8_t)z[4 * q] | (uint32_t)(uint8_t)z[4 * q + 1] << 8 |
-              (uint32_t)(uint8_t)z[4 * q + 2] << 16 | (uint32_t)(uint8_t)z[4 * q + 3] << 24;
+    typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
+    const uint32_t n8 = cols * (kDim / 8), inv = (1u << 20) / n8 + 1;
+    for (uint32_t i = threadIdx.x; i < R_t * n8; i += 256) {
+      const uint32_t r = i * inv >> 20, k = i - r * n8;
+      const u32x2a z = *(const u32x2a*)(zs + r * row_bytes + k * 8);
+      *(u32x2u*)(zout + (blk0 + (int64_t)r * a.nb) * kDim + k * 8) = u32x2u{z.x, z.y};
+    }
   }
-  const uint32_t e = e16 >> 4;
-  if (cout) cout[bi] = (uint16_t)(e & 511u);
-  if (gout) gout[bi] = (uint8_t)(e >> 9);
+  if (cout || gout) {
+    const uint32_t inv = (1u << 20) / cols + 1;
+    for (uint32_t i = threadIdx.x; i < R_t * cols; i += 256) {
+      const uint32_t r = i * inv >> 20, c = i - r * cols;
+      const uint32_t e = es[r * W + c];
+      const int64_t bi = blk0 + (int64_t)r * a.nb + c;
+      if (cout) cout[bi] = (uint16_t)(e & 511u);
+      if (gout) gout[bi] = (uint8_t)(e >> 9);
+    }
+  }
 }
 
 // ------------------------------------------------------ FP16 GEMV control
@@ -1640,9 +1698,12 @@ static int launch_batch_mx(const GemvArgs& a, hipStream_t st) {
 
 template <int LAYOUT>
 static int launch_decode(const GemvArgs& a, int8_t* z, uint16_t* c, uint8_t* g, hipStream_t st) {
-  const int64_t n = a.M * a.nb;
-  hipLaunchKernelGGL(decode_kernel<LAYOUT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                     a, z, c, g);
+  const int64_t chunks = (a.groups + kDecodeUnits - 1) / kDecodeUnits;
+  const int W = kDecodeUnits * a.C;
+  const size_t shmem = (size_t)a.R * (W * kDim + kDecodePad + W * sizeof(uint16_t));
+  if (a.tiles * chunks > 0x7fffffff) return set_error(LEECH_E_SHAPE, "matrix too large");
+  hipLaunchKernelGGL(decode_kernel<LAYOUT>, dim3((unsigned)(a.tiles * chunks)), dim3(256), shmem, st,
+                     a, (uint32_t)chunks, z, c, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail("decode launch", e);
   return LEECH_OK;

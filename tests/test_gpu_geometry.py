@@ -24,7 +24,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import paper_2609_02652_amd as P  # noqa: E402
-from paper_2609_02652_amd import synth  # noqa: E402
+from paper_2609_02652_amd import _lib, synth  # noqa: E402
 from oracle import decode as D  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -161,3 +161,30 @@ def test_groups_sharing_tiles(dev, dcb, case):
             y_two = mat.gemv_grouped(P.rotate_x(raw, None, mat.Kpad), parts, cens).cpu().numpy()
             assert np.array_equal(y_rot.view(np.uint32), y_two.view(np.uint32))
         assert np.array_equal(y.view(np.uint32), ref.view(np.uint32)), name
+
+
+@pytest.mark.parametrize("step", [-1, 0, 1])
+@pytest.mark.parametrize("geo", [(1, 64), (3, 20), (16, 4)], ids=["1x64", "3x20", "16x4"])
+def test_decode_runs(dev, dcb, geo, step):
+    """Whole-matrix decode where a row has one block fewer than a workgroup's
+    eight units, just as many, and one more; z at an address that is a multiple
+    of 4 only, and each output on its own.  Nothing past an output is written."""
+    C, R = geo
+    M, nb = R + 3, 8 * C + step
+    say(f"[decode runs] {geo} {M}x{24 * nb}")
+    inp = synth.make_gemv_inputs(M, 24 * nb, seed=33, name="decode-runs")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z)
+    mat = P.LeechMatrix.from_fields(dcb, P.PLANES14, cls, inp.gain, sm, lv, inp.scale, dev,
+                                    geometry=geo)
+    n = M * nb
+    z = torch.full((24 * n + 8,), 99, dtype=torch.int8, device=dev)
+    c = torch.full((n + 1,), 999, dtype=torch.int16, device=dev)
+    g = torch.full((n + 1,), 9, dtype=torch.uint8, device=dev)
+    for zp, cp, gp in ((z.data_ptr() + 4, 0, 0), (0, c.data_ptr(), 0), (0, 0, g.data_ptr())):
+        _lib.decode_blocks(mat.desc, mat.main.data_ptr(), 0, 0, dcb.table.data_ptr(), 0, zp, cp, gp,
+                           torch.cuda.current_stream().cuda_stream)
+    z, c, g = z.cpu().numpy(), c.cpu().numpy(), g.cpu().numpy()
+    assert np.array_equal(z[4:-4].reshape(M, nb, 24), inp.z)
+    assert (z[:4] == 99).all() and (z[-4:] == 99).all()
+    assert np.array_equal(c[:-1].reshape(M, nb), cls) and c[-1] == 999
+    assert np.array_equal(g[:-1].reshape(M, nb), inp.gain) and g[-1] == 9
