@@ -161,6 +161,24 @@ def test_fp16_control(dev, M, K):
     assert e["max_abs_err"] <= TOL_PAPER
 
 
+@pytest.mark.parametrize("K", [504, 512, 2040, 2048, 2056, 4096, 4104])
+def test_fp16_control_chunks(dev, K):
+    """Rows that end at, before and after a round of the kernel's 512-wide
+    chunks, nine rows in workgroups of eight, NaN after the last row."""
+    M = 9
+    say(f"[fp16 chunks] M={M} K={K}")
+    rng = np.random.default_rng(K)
+    W = (rng.standard_normal((M, K)) * 0.05).astype(np.float16)
+    x = rng.standard_normal(K).astype(np.float16)
+    buf = torch.full((M * K + 4096,), float("nan"), dtype=torch.float16, device=dev)
+    buf[:M * K] = torch.from_numpy(W).to(dev).flatten()
+    y = P.fp16_gemv(buf[:M * K].view(M, K), torch.from_numpy(x).to(dev)).cpu().numpy()
+    # f32 sums of K products: K roundings of at most 2^-24 of the sum of magnitudes
+    y64 = W.astype(np.float64) @ x.astype(np.float64)
+    bound = K * 2.0 ** -24 * (np.abs(W.astype(np.float64)) @ np.abs(x.astype(np.float64)))
+    assert (np.abs(y - y64) <= bound).all()
+
+
 @pytest.mark.parametrize("M,K", [(65, 24 * 17), (4096, 4096)])
 def test_noweights_control(dev, dcb, M, K):
     say(f"[noweights] M={M} K={K}")
