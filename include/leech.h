@@ -356,9 +356,10 @@ int leech_set_exception_mode(int mode);
 
 /* Products of leech_gemv_batch calls with batch > 1 enqueued from this call on
  * (process-wide; §6 "Batching").  LEECH_BATCH_AUTO (default): each decoded
- * block meets its activations on the matrix cores (16-block 4×4×4 binary16
- * products with f32 accumulation, one block's 24 products per output, so the
- * block's scale and class factor still multiply its f32 dot product); Y[b] is
+ * block meets its activations on the matrix cores (4×4×4, 16×16×4 or
+ * 32×32×4 binary16 products, which round alike, with f32 accumulation, one
+ * block's 24 products per output, so the block's scale and class factor still
+ * multiply its f32 dot product); Y[b] is
  * then within rounding of leech_gemv on X[b] (the matrix core sums a block's
  * products in its own order) and bit-identical for a given X[b] whatever the
  * batch size or X[b]'s position.  LEECH_BATCH_DOT2: v_dot2 per activation,

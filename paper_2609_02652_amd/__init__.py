@@ -153,7 +153,7 @@ class LeechMatrix:
 
     def gemv_batch(self, X, Y=None, centroids=(1.0, 1.0), stream=None):
         """Y[b] = W X[b]: X fp16 [B, Kpad] device tensor (row stride a multiple
-        of 8), Y f32 [B, M]; each block decoded once for up to 16 activations,
+        of 8), Y f32 [B, M]; each block decoded once for a tile of activations,
         multiplied on the matrix cores or with v_dot2 (set_batch_mode)."""
         torch = _torch()
         if X.dtype != torch.float16 or X.dim() != 2 or X.shape[1] != self.Kpad or X.stride(1) != 1:

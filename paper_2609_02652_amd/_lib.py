@@ -25,7 +25,8 @@ ERRORS = {0: "OK", -1: "LEECH_E_ARG", -2: "LEECH_E_LAYOUT", -3: "LEECH_E_SHAPE",
 EXPORTS = ["leech_last_error", "leech_codebook_build", "leech_codebook_free",
            "leech_codebook_info", "leech_codebook_class", "leech_codebook_table",
            "leech_fields_from_points", "leech_expand_layout", "leech_layout_scales",
-           "leech_layout_scales_device", "leech_host_decode_layout", "leech_gemv", "leech_gemv_grouped", "leech_decode_blocks",
+           "leech_layout_scales_device", "leech_host_decode_layout", "leech_gemv",
+           "leech_gemv_grouped", "leech_decode_blocks",
            "leech_fp16_gemv_ref", "leech_noweights_ctrl", "leech_rotate_x",
            "leech_index_encode", "leech_index_decode", "leech_planes14_desc",
            "leech_transcode_planes14", "leech_set_exception_mode", "leech_gemv_batch",

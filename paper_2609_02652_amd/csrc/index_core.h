@@ -1,8 +1,8 @@
 // Format-v1 block codes (§2.1 "What a Λ24 index is"; §2.2 "Unfolding at load
 // time"): the 47-bit direction index of a point of the ball Λ24(12) plus the
-// gain bit, and its conversion to and from decoded fields.  Shared by the host
-// library (encode, decode) and the GPU transcoder (decode), which read the
-// same table.  Not part of the public ABI.
+// gain bit, and its conversion to and from decoded fields: the host library's
+// encode and decode, and the table and bit routines that the GPU transcoder's
+// own decode shares with them.  Not part of the public ABI.
 //
 // The order (mixed radix, most significant digit first):
 //   index = offset(class) + r, classes in id order;
