@@ -88,6 +88,9 @@ class LeechMatrix:
             raise ValueError("codes must be a contiguous int64 tensor [M, nb]")
         M, nb = codes.shape
         desc = planes14_desc(M, nb * 24)
+        rowmajor = np.ascontiguousarray(scale_rowmajor, np.float16).reshape(-1)[: M * nb]
+        if rowmajor.size < M * nb:
+            raise ValueError("scale_rowmajor must hold one fp16 scale per block")
         dev = codes.device
         main = torch.empty(desc.main_bytes, dtype=torch.uint8, device=dev)
         bad = torch.empty(1, dtype=torch.int32, device=dev)
@@ -95,9 +98,6 @@ class LeechMatrix:
                                 bad.data_ptr(), _stream(stream))
         # the scales take their storage order on the device; on the current
         # stream, like the copy, so that the wait below covers them
-        rowmajor = np.ascontiguousarray(scale_rowmajor, np.float16).reshape(-1)[: M * nb]
-        if rowmajor.size < M * nb:
-            raise ValueError("scale_rowmajor must hold one fp16 scale per block")
         rows = _dev(rowmajor, dev)
         scale = torch.empty_like(rows)
         _lib.layout_scales_device(desc, rows.data_ptr(), scale.data_ptr(), _stream(None))

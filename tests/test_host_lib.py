@@ -382,3 +382,20 @@ def test_mode_setters_reject_unknown_values():
         P.set_exception_mode(5)
     P.set_batch_mode(P.BATCH_DOT2)
     P.set_batch_mode(P.BATCH_AUTO)
+
+
+def test_from_codes_refuses_short_scales_before_any_launch(cb, monkeypatch):
+    """The scales are checked before the transcoder is enqueued: a refusal after
+    it would give the outputs back while they are being written."""
+    torch = pytest.importorskip("torch")
+    launched = []
+    monkeypatch.setattr(_lib, "transcode_planes14", lambda *a: launched.append(a))
+    monkeypatch.setattr(P, "_stream", lambda stream: 0)
+
+    class Table:
+        index = torch.zeros(16, dtype=torch.uint8)
+
+    with pytest.raises(ValueError, match="one fp16 scale per block"):
+        P.LeechMatrix.from_codes(Table, torch.zeros((4, 3), dtype=torch.int64),
+                                 np.zeros(11, np.float16))
+    assert not launched
