@@ -92,16 +92,32 @@ class LeechMatrix:
         if rowmajor.size < M * nb:
             raise ValueError("scale_rowmajor must hold one fp16 scale per block")
         dev = codes.device
-        main = torch.empty(desc.main_bytes, dtype=torch.uint8, device=dev)
-        bad = torch.empty(1, dtype=torch.int32, device=dev)
-        _lib.transcode_planes14(desc, dcb.index.data_ptr(), codes.data_ptr(), main.data_ptr(),
-                                bad.data_ptr(), _stream(stream))
-        # the scales take their storage order on the device; on the current
-        # stream, like the copy, so that the wait below covers them
-        rows = _dev(rowmajor, dev)
-        scale = torch.empty_like(rows)
-        _lib.layout_scales_device(desc, rows.data_ptr(), scale.data_ptr(), _stream(None))
-        n_bad = int(bad.item())
+        with torch.cuda.device(dev):
+            main = torch.empty(desc.main_bytes, dtype=torch.uint8, device=dev)
+            bad = torch.empty(1, dtype=torch.int32, device=dev)
+            # A caller's stream runs between two waits: for the codes and the
+            # two allocations before the transcoder, and by the current stream
+            # for the transcoder, whether it was launched whole or not, before
+            # anything reads or reuses its outputs.
+            current = _stream(None)
+            handle, side = current if stream is None else _stream(stream), None
+            if handle != current:
+                # (an ExternalStream of 0 would be a new stream)
+                side = (torch.cuda.ExternalStream(handle, device=dev) if handle
+                        else torch.cuda.default_stream(dev))
+                side.wait_stream(torch.cuda.current_stream())
+            try:
+                _lib.transcode_planes14(desc, dcb.index.data_ptr(), codes.data_ptr(),
+                                        main.data_ptr(), bad.data_ptr(), handle)
+            finally:
+                if side is not None:
+                    torch.cuda.current_stream().wait_stream(side)
+            # the scales take their storage order on the device; on the current
+            # stream, like the copy: the wait for `bad` covers everything
+            rows = _dev(rowmajor, dev)
+            scale = torch.empty_like(rows)
+            _lib.layout_scales_device(desc, rows.data_ptr(), scale.data_ptr(), current)
+            n_bad = int(bad.item())
         if n_bad:
             raise LeechError(-4, f"{n_bad} of {M * nb} block codes are not format-v1 codes")
         empty = torch.empty(0, dtype=torch.uint8, device=dev)

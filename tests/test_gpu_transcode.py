@@ -164,6 +164,41 @@ def test_transcode_tile_past_32_bits(dev, dcb):
     assert bool((tail[14 * rest:] == 0).all())
 
 
+@pytest.mark.parametrize("kind", ["stream", "handle", "default"])
+def test_from_codes_on_another_stream(dev, dcb, kind):
+    """With stream= other than the current one, and work ahead of the transcoder
+    on both: the codes are read after the current stream has written them,
+    invalid ones are counted, and the matrix is whole on return.  A stale or
+    early count would fail the valid matrix or pass the invalid one."""
+    say(f"[transcode] caller's stream: {kind}")
+    M, K = 1024, 24 * 64
+    inp = synth.make_gemv_inputs(M, K, seed=9, name="transcode-stream")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z)
+    codes = P.index_encode(dcb.cb, cls, inp.gain, sm, lv).view(np.int64)
+    ref = P.LeechMatrix.from_fields(dcb, P.PLANES14, cls, inp.gain, sm, lv, inp.scale, dev)
+    good = torch.from_numpy(codes).to(dev)
+    wrong = good.clone()
+    wrong[5, 7] = wrong[M - 1, 3] = 1 << 50
+    work = torch.randn(4096, 4096, device=dev)
+    side, outer = torch.cuda.Stream(dev), torch.cuda.Stream(dev)
+    torch.cuda.synchronize()
+    # "default": the current stream is another one, the caller's the default
+    given = {"stream": side, "handle": side.cuda_stream, "default": torch.cuda.default_stream(dev)}
+    with torch.cuda.stream(outer if kind == "default" else torch.cuda.current_stream(dev)):
+        for turn in range(4):
+            with torch.cuda.stream(torch.cuda.default_stream(dev) if kind == "default" else side):
+                (work @ work).sum()
+            live = torch.zeros_like(good)       # not codes of these points until the copy
+            (work @ work).sum()
+            live.copy_(wrong if turn % 2 else good)
+            if turn % 2:
+                with pytest.raises(P.LeechError, match="2 of"):
+                    P.LeechMatrix.from_codes(dcb, live, inp.scale, stream=given[kind])
+            else:
+                mat = P.LeechMatrix.from_codes(dcb, live, inp.scale, stream=given[kind])
+                assert torch.equal(mat.main, ref.main) and torch.equal(mat.scale, ref.scale)
+
+
 def host_storage_index(desc):
     """Storage slot of block (r, j) in the wave-tile order (rows grouped in
     tiles of tile_rows, units of lane_cols columns, stored row by row)."""
