@@ -42,8 +42,10 @@ def _stream(stream):
 
 def _dev(arr: np.ndarray, device):
     torch = _torch()
-    t = torch.from_numpy(np.ascontiguousarray(arr).view(np.uint8))
-    return t.to(device)
+    # a tensor over a read-only array (memory-mapped weights) would warn, or
+    # raise where warnings are errors
+    arr = np.require(arr, requirements=("C", "W")).view(np.uint8)
+    return torch.from_numpy(arr).to(device)
 
 
 class DeviceCodebook:

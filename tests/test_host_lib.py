@@ -399,3 +399,19 @@ def test_from_codes_refuses_short_scales_before_any_launch(cb, monkeypatch):
         P.LeechMatrix.from_codes(Table, torch.zeros((4, 3), dtype=torch.int64),
                                  np.zeros(11, np.float16))
     assert not launched
+
+
+@pytest.mark.filterwarnings("error")
+@pytest.mark.parametrize("shape", [(4, 6), (0,)])
+def test_upload_takes_read_only_arrays(shape):
+    """Memory-mapped scales are read-only: their upload gives their bytes, with no
+    warning, and a tensor that does not share them."""
+    torch = pytest.importorskip("torch")
+    arr = np.arange(int(np.prod(shape)), dtype=np.float16).reshape(shape)
+    for a in (arr.copy(), arr.copy().T):
+        a.flags.writeable = False
+        t = P._dev(a, "cpu")
+        assert t.dtype == torch.uint8
+        assert np.array_equal(t.numpy().reshape(-1), np.ascontiguousarray(a).view(np.uint8).reshape(-1))
+        t.fill_(255)
+        assert np.array_equal(a.reshape(-1), (arr if a.flags.c_contiguous else arr.T).reshape(-1))
