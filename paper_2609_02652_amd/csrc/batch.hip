@@ -45,6 +45,7 @@ typedef float f32x32 __attribute__((ext_vector_type(32)));
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
+constexpr int64_t kMaxGroups = 0xFFFFFFFFll / kThreads;   // a launch has fewer than 2^32 threads
 constexpr uint32_t kOutOfRange = 0x7FFFFFF0u;   // buffer offset past any descriptor's end
 
 struct BatchArgs {
@@ -458,17 +459,29 @@ int launch_tile(BatchArgs a, hipStream_t st) {
       return set_error(LEECH_E_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
   }
   const int64_t row_blocks = ((int64_t)a.M + RW - 1) / RW;
-  const int64_t batch_tiles = (a.batch + NB - 1) / NB;
-  const int64_t grid = batch_tiles > 1 ? (row_blocks + 7) / 8 * 8 * batch_tiles : row_blocks;
-  if (grid > 0x7fffffff) return set_error(LEECH_E_SHAPE, "batch too large for one launch");
+  if (row_blocks > kMaxGroups) return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
+  // As many batch tiles a launch as it can hold; a launch of several has a
+  // multiple of eight row blocks.
+  const int64_t padded = (row_blocks + 7) / 8 * 8;
+  const int64_t most = std::max<int64_t>(1, kMaxGroups / padded) * NB;
+  const uint16_t* const x = a.x;
+  float* const y = a.y;
+  const int64_t batch = a.batch;
   a.row_blocks = (int)row_blocks;
-  a.batch_tiles = (int)batch_tiles;
-  a.inv_t32 = (uint32_t)(((1ull << 32) + batch_tiles - 1) / batch_tiles);
-  hipLaunchKernelGGL((batch_kernel<C, RW, NB, D, WPS>), dim3((unsigned)grid), dim3(kThreads), shmem,
-                     st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess)
-    return set_error(LEECH_E_HIP, std::string("batch launch: ") + hipGetErrorString(e));
+  for (int64_t b0 = 0; b0 < batch; b0 += most) {
+    a.x = x + b0 * a.ldx;
+    a.y = y + b0 * a.ldy;
+    a.batch = (int)std::min(most, batch - b0);
+    const int64_t batch_tiles = ((int64_t)a.batch + NB - 1) / NB;
+    a.batch_tiles = (int)batch_tiles;
+    a.inv_t32 = (uint32_t)(((1ull << 32) + batch_tiles - 1) / batch_tiles);
+    const int64_t grid = batch_tiles > 1 ? padded * batch_tiles : row_blocks;
+    hipLaunchKernelGGL((batch_kernel<C, RW, NB, D, WPS>), dim3((unsigned)grid), dim3(kThreads),
+                       shmem, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+      return set_error(LEECH_E_HIP, std::string("batch launch: ") + hipGetErrorString(e));
+  }
   return LEECH_OK;
 }
 
@@ -489,7 +502,7 @@ constexpr Tiles kTiles[] = {{1, {6464, 6432, 6416, 3216}}, {2, {6432, 3232, 3216
 // 32 (128) 12.2; 64: 32 × 32 13.1, 64 × 32 (128) 17.5; 128: 64 × 32 18.8, 32 × 32
 // 23.4; 5120×17424 (3 × 20), 32: 32 × 32 (160) 45.4, 64 × 32 (80) 68.7;
 // 14336×4104 (1 × 64), 64: 64 × 64 31.7, 64 × 32 38.4.
-int choose_tile(int C, int64_t M, int batch) {
+int choose_tile(int C, int64_t M, int64_t batch) {
   int best = 0;
   for (const Tiles& t : kTiles)
     if (t.C == C)

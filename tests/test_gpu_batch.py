@@ -204,6 +204,23 @@ def test_wide_batch_tiles(dev, dcb, geo, M, K, B):
     assert torch.all(Y[:, M] == -3.0)
 
 
+def test_batch_past_one_launch(dev, dcb):
+    """One row and 2^24 + 37 activations: 8 · (2^20 + 3) workgroups of 512
+    threads, more than the 2^32 threads of a launch, so the batch takes two.
+    The same bits as in calls of 2^20 activations."""
+    B = (1 << 24) + 37
+    say(f"[batch] 1x24 B={B}")
+    inp, mat = build(dev, dcb, 1, 24, 7, geometry=(16, 4))
+    g = torch.Generator(device=dev).manual_seed(1)
+    X = torch.randn(B, 24, generator=g, device=dev, dtype=torch.float16)
+    Y = torch.full((B + 1, 1), -3.0, dtype=torch.float32, device=dev)
+    mat.gemv_batch(X, Y[:B], centroids=CEN)
+    for b0 in range(0, B, 1 << 20):
+        part = mat.gemv_batch(X[b0:b0 + (1 << 20)], centroids=CEN)
+        assert torch.equal(Y[b0:b0 + part.shape[0]].view(torch.int32), part.view(torch.int32)), b0
+    assert float(Y[B]) == -3.0
+
+
 def test_batch_mode_rejects_unknown(dev):
     with pytest.raises(P.LeechError):
         P.set_batch_mode(7)
