@@ -1360,14 +1360,14 @@ constexpr int kDecodeUnits = 8;             // units of a workgroup
 constexpr int kDecodePad = 8;               // bytes after each row's run, against bank conflicts
 
 template <int LAYOUT>
-__global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t chunks, int8_t* zout,
-                                                     uint16_t* cout, uint8_t* gout) {
+__global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t tile0, uint32_t chunks,
+                                                     int8_t* zout, uint16_t* cout, uint8_t* gout) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int W = kDecodeUnits * a.C;
   const int row_bytes = W * kDim + kDecodePad;
   uint8_t* const zs = smem;
   uint16_t* const es = (uint16_t*)(smem + a.R * row_bytes);
-  const int tile = (int)(blockIdx.x / chunks);
+  const int tile = (int)(tile0 + blockIdx.x / chunks);
   const int g0 = (int)(blockIdx.x % chunks) * kDecodeUnits;
   const int groups = (int)a.groups;
   const int R_t = (int)min((int64_t)a.R, a.M - (int64_t)tile * a.R);
@@ -1725,11 +1725,16 @@ static int launch_decode(const GemvArgs& a, int8_t* z, uint16_t* c, uint8_t* g, 
   const int64_t chunks = (a.groups + kDecodeUnits - 1) / kDecodeUnits;
   const int W = kDecodeUnits * a.C;
   const size_t shmem = (size_t)a.R * (W * kDim + kDecodePad + W * sizeof(uint16_t));
-  if (a.tiles * chunks > 0x7fffffff) return set_error(LEECH_E_SHAPE, "matrix too large");
-  hipLaunchKernelGGL(decode_kernel<LAYOUT>, dim3((unsigned)(a.tiles * chunks)), dim3(256), shmem, st,
-                     a, (uint32_t)chunks, z, c, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail("decode launch", e);
+  // whole tiles a launch, which has fewer than 2^32 threads (a row has at most
+  // 2^24 columns, 2^21 chunks)
+  const int64_t most = 0xFFFFFFFFll / 256 / chunks;
+  for (int64_t tile0 = 0; tile0 < a.tiles; tile0 += most) {
+    const int64_t tiles = std::min(most, a.tiles - tile0);
+    hipLaunchKernelGGL(decode_kernel<LAYOUT>, dim3((unsigned)(tiles * chunks)), dim3(256), shmem,
+                       st, a, (uint32_t)tile0, (uint32_t)chunks, z, c, g);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail("decode launch", e);
+  }
   return LEECH_OK;
 }
 

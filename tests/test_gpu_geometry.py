@@ -188,3 +188,24 @@ def test_decode_runs(dev, dcb, geo, step):
     assert (z[:4] == 99).all() and (z[-4:] == 99).all()
     assert np.array_equal(c[:-1].reshape(M, nb), cls) and c[-1] == 999
     assert np.array_equal(g[:-1].reshape(M, nb), inp.gain) and g[-1] == 9
+
+
+def test_decode_past_one_launch(dev, dcb):
+    """2^26 + 5 rows of one block in tiles of four: 2^24 + 2 workgroups of 256
+    threads, more than the 2^32 threads of a launch, so the decode takes two.
+    With one column the stream is in row order: the records of a repeated pool."""
+    M, pool = (1 << 26) + 5, 4099
+    say(f"[decode] {M}x24")
+    inp = synth.make_gemv_inputs(pool, 24, seed=3, name="decode-long")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z)
+    _, main, _, _ = P.expand_layout(dcb.cb, P.PLANES14, cls, inp.gain, sm, lv, (16, 4))
+    desc = P.planes14_desc(M, 24, (16, 4))
+    rows = torch.arange(M, device=dev) % pool
+    recs = torch.from_numpy(main[:14 * pool].reshape(pool, 14)).to(dev)
+    stream = torch.zeros(desc.main_bytes, dtype=torch.uint8, device=dev)
+    stream[:14 * M].view(M, 14).copy_(recs[rows])
+    empty = torch.empty(0, dtype=torch.uint8, device=dev)
+    z, c, g = P.LeechMatrix(desc, stream, empty, empty, None, dcb).decode()
+    for got, want in ((z[:, 0], inp.z[:, 0]), (c[:, 0], cls[:, 0].astype(np.int16)),
+                      (g[:, 0], inp.gain[:, 0])):
+        assert torch.equal(got, torch.from_numpy(np.ascontiguousarray(want)).to(dev)[rows])
