@@ -358,16 +358,16 @@ __global__ __launch_bounds__(kTcThreads) void transcode_planes14_kernel(Transcod
 
 __global__ void clear_u32_kernel(uint32_t* p) { *p = 0; }
 
-// The block scales in storage order: a thread a slot, so the writes are
-// contiguous and the reads gather; bound by its launch (11 MB of scales and less
-// in real matrices).
-__global__ __launch_bounds__(256) void scale_order_kernel(TranscodeArgs a,
+// The block scales in storage order: a thread a slot, from slot `first` on, so
+// the writes are contiguous and the reads gather; bound by its launch (11 MB of
+// scales and less in real matrices).
+__global__ __launch_bounds__(256) void scale_order_kernel(TranscodeArgs a, uint64_t first,
                                                           const uint16_t* __restrict__ in,
                                                           uint16_t* __restrict__ out) {
-  const uint64_t s0 = (uint64_t)blockIdx.x * 256;
+  const uint64_t s0 = first + (uint64_t)blockIdx.x * 256;
   const uint64_t t0 = s0 / a.tile_blocks;
-  for (int k = threadIdx.x; k < 256 && s0 + k < a.n; k += blockDim.x)
-    out[s0 + k] = in[block_of_slot(a, t0, s0 - t0 * a.tile_blocks, k)];
+  const int k = threadIdx.x;
+  if (s0 + k < a.n) out[s0 + k] = in[block_of_slot(a, t0, s0 - t0 * a.tile_blocks, k)];
 }
 
 int tc_fail(const char* what, hipError_t e) {
@@ -420,12 +420,14 @@ extern "C" int leech_layout_scales_device(const leech_layout_desc* desc,
     return set_error(LEECH_E_ARG, "misaligned device pointer");
   const TranscodeArgs a =
       slot_args(Geometry(desc->M, desc->nb, desc->lane_cols, desc->tile_rows));
-  const uint64_t blocks = (a.n + 255) / 256;
-  if (blocks > 0x7fffffff) return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
-  hipLaunchKernelGGL(scale_order_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream,
-                     a, d_scale_rowmajor, d_scale_out);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return tc_fail("scale order launch", e);
+  const uint64_t most = 0xFFFFFF00ull;      // a launch has fewer than 2^32 threads
+  for (uint64_t first = 0; first < a.n; first += most) {
+    const uint64_t blocks = (std::min(most, a.n - first) + 255) / 256;
+    hipLaunchKernelGGL(scale_order_kernel, dim3((unsigned)blocks), dim3(256), 0,
+                       (hipStream_t)stream, a, first, d_scale_rowmajor, d_scale_out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return tc_fail("scale order launch", e);
+  }
   return LEECH_OK;
 }
 

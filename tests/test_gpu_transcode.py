@@ -164,6 +164,32 @@ def test_transcode_tile_past_32_bits(dev, dcb):
     assert bool((tail[14 * rest:] == 0).all())
 
 
+def test_scales_past_one_launch(dev):
+    """65,541 rows of 65,536 blocks, more than 2^32: the storage order takes two
+    launches.  Each tile's slots hold its rows' scales by column group, row and
+    column."""
+    M, nb, (C, R) = 65541, 65536, (16, 4)
+    if torch.cuda.mem_get_info(dev)[0] < 40 << 30:
+        pytest.skip("needs 40 GB of device memory")
+    say(f"[scales] {M}x{24 * nb}")
+    desc = P.planes14_desc(M, 24 * nb, (C, R))
+    col = torch.arange(nb, device=dev, dtype=torch.int32)
+    rows = torch.empty((M, nb), dtype=torch.int16, device=dev)
+    for r0 in range(0, M, 4096):
+        r = torch.arange(r0, min(M, r0 + 4096), device=dev, dtype=torch.int32)
+        rows[r0:r0 + 4096] = (r[:, None] * 40503 + col * 30011 + (col >> 8)).to(torch.int16)
+    out = torch.full((M * nb + 1,), 77, dtype=torch.int16, device=dev)
+    _lib.layout_scales_device(desc, rows.data_ptr(), out.data_ptr())
+    full = M // R * R
+    got = out[:full * nb].view(full // R, nb // C, R, C)
+    want = rows[:full].view(full // R, R, nb // C, C)
+    for t in range(0, full // R, 1024):
+        assert torch.equal(got[t:t + 1024], want[t:t + 1024].transpose(1, 2)), t
+    assert torch.equal(out[full * nb:-1].view(nb // C, M - full, C),
+                       rows[full:].view(M - full, nb // C, C).transpose(0, 1))
+    assert int(out[-1]) == 77
+
+
 @pytest.mark.parametrize("kind", ["stream", "handle", "default"])
 def test_from_codes_on_another_stream(dev, dcb, kind):
     """With stream= other than the current one, and work ahead of the transcoder
