@@ -1524,6 +1524,10 @@ __global__ __launch_bounds__(512) void fp16_gemv_kernel(const uint16_t* __restri
 // How GEMV launches enqueued from now on decode Golay70 exceptions.
 static std::atomic<int> g_exc_mode{LEECH_EXC_HOISTED};
 
+// A launch has fewer than 2^32 threads; the runtime cuts a larger grid without
+// an error.
+constexpr int64_t kMaxLaunchThreads = 0xFFFFFFFFll;
+
 static int hip_fail(const char* what, hipError_t e) {
   return set_error(LEECH_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -1590,6 +1594,8 @@ static size_t gemv_lds_bytes(const GemvArgs& a) {
 template <int LAYOUT, bool EVEN, int NB, int XPER, bool ROT = false, int PRO = 0,
           bool PHASE = false, bool MX = false>
 static int launch_gemv_kernel(const GemvArgs& a, size_t shmem, hipStream_t st) {
+  if (a.tiles * 64 * a.waves > kMaxLaunchThreads)
+    return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
   const void* fn;
   if constexpr (MX)
     fn = (const void*)gemv_kernel_mx<LAYOUT, EVEN, NB, XPER>;
@@ -1725,9 +1731,8 @@ static int launch_decode(const GemvArgs& a, int8_t* z, uint16_t* c, uint8_t* g, 
   const int64_t chunks = (a.groups + kDecodeUnits - 1) / kDecodeUnits;
   const int W = kDecodeUnits * a.C;
   const size_t shmem = (size_t)a.R * (W * kDim + kDecodePad + W * sizeof(uint16_t));
-  // whole tiles a launch, which has fewer than 2^32 threads (a row has at most
-  // 2^24 columns, 2^21 chunks)
-  const int64_t most = 0xFFFFFFFFll / 256 / chunks;
+  // whole tiles a launch (a row has at most 2^24 columns, 2^21 chunks)
+  const int64_t most = kMaxLaunchThreads / 256 / chunks;
   for (int64_t tile0 = 0; tile0 < a.tiles; tile0 += most) {
     const int64_t tiles = std::min(most, a.tiles - tile0);
     hipLaunchKernelGGL(decode_kernel<LAYOUT>, dim3((unsigned)(tiles * chunks)), dim3(256), shmem,
@@ -1975,6 +1980,8 @@ int leech_fp16_gemv_ref(int64_t M, int64_t K, const uint16_t* d_W, const uint16_
     if (e != hipSuccess) return hip_fail("hipFuncSetAttribute", e);
   }
   const int waves = 8;
+  if ((M + waves - 1) / waves > kMaxLaunchThreads / (64 * waves))
+    return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
   hipLaunchKernelGGL(fp16_gemv_kernel, dim3((unsigned)((M + waves - 1) / waves)), dim3(64 * waves),
                      shmem, (hipStream_t)stream, d_W, d_x, d_y, M, K);
   hipError_t e = hipGetLastError();

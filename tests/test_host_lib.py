@@ -415,3 +415,18 @@ def test_upload_takes_read_only_arrays(shape):
         assert np.array_equal(t.numpy().reshape(-1), np.ascontiguousarray(a).view(np.uint8).reshape(-1))
         t.fill_(255)
         assert np.array_equal(a.reshape(-1), (arr if a.flags.c_contiguous else arr.T).reshape(-1))
+
+
+@pytest.mark.parametrize("case", ["gemv", "noweights", "fp16"])
+def test_grids_past_a_launch_are_refused(case):
+    """A launch has fewer than 2^32 threads, and the runtime cuts a larger grid
+    without an error; such a matrix is refused before the launch (the pointers
+    here are never read)."""
+    # 2^23 + 1 tiles of four rows, eight waves a tile; 2^26 + 8 fp16 rows, a wave each
+    desc = P.planes14_desc((1 << 25) + 4, 24 * 128, (16, 4))
+    call = {"gemv": lambda: _lib.gemv(desc, 16, 0, 0, 16, 0, 16, (1.0, 1.0), 16, 16),
+            "noweights": lambda: _lib.noweights_ctrl(desc, 16, 16),
+            "fp16": lambda: _lib.fp16_gemv_ref((1 << 26) + 8, 8, 16, 16, 16)}[case]
+    with pytest.raises(P.LeechError, match="too large for one launch") as e:
+        call()
+    assert e.value.code == -3
