@@ -278,11 +278,14 @@ __global__ __launch_bounds__(kThreads, WPS) void batch_kernel(BatchArgs a) {
       const uint32_t nl = (uint32_t)(n + p), k = nl / C;
       const uint32_t g = (uint32_t)wave + kWaves * k, j = g * C + (nl - k * C);
       const uint32_t idx = __umul24(g, lane_group) + lane_row + j - ((int)g == glast ? lane_skip : 0u);
-      const uint32_t off = __umul24(idx, (uint32_t)kPlanes14Bytes);
-      // Past the last column nothing is read: such columns have a scale of zero
-      // and multiply zero activations.
+      // Past the last column: the buffer's first record, with a scale of zero
+      // and zero activations.  (A record of zeros would bring in class 0's
+      // factor, whose centroid may be one that no block of the matrix has: not
+      // finite, it would turn the zero into a NaN.)  Past the wave's last step
+      // nothing is read, nor used.
       const bool live = (int)j < nb;
-      vo = live ? off & ~3u : kOutOfRange;
+      const uint32_t off = live ? __umul24(idx, (uint32_t)kPlanes14Bytes) : 0u;
+      vo = step < steps ? off & ~3u : kOutOfRange;
       s.sh = (off & 2u) << 3;
       vs = live ? idx * 2u : kOutOfRange;
       so = ss = 0;

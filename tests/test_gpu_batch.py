@@ -204,6 +204,25 @@ def test_wide_batch_tiles(dev, dcb, geo, M, K, B):
     assert torch.all(Y[:, M] == -3.0)
 
 
+@pytest.mark.parametrize("geo", [(1, 64), (2, 32), (3, 20), (4, 16), (8, 8), (16, 4)])
+def test_batch_unused_centroid(dev, dcb, geo):
+    """No block has gain bit 0, so its centroid does not matter, NaN included:
+    batches of every kernel give the bits of a finite one, with columns to spare
+    in the last group and waves without a unit."""
+    C, R = geo
+    M, nb = R + 5, 9 * C + max(1, C - 1)
+    say(f"[batch centroid] {geo} {M}x{24 * nb}")
+    inp = synth.make_gemv_inputs(M, 24 * nb, seed=5, name="batch-centroid")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z)
+    mat = P.LeechMatrix.from_fields(dcb, P.PLANES14, cls, np.ones_like(inp.gain), sm, lv,
+                                    inp.scale, dev, geometry=geo)
+    X = torch.from_numpy(activations(24 * nb, 33, seed=nb)).to(dev)
+    for B in (2, 4, 5, 16, 33):
+        want = mat.gemv_batch(X[:B], centroids=(1.0, 1.25))
+        got = mat.gemv_batch(X[:B], centroids=(float("nan"), 1.25))
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), B
+
+
 def test_batch_past_one_launch(dev, dcb):
     """One row and 2^24 + 37 activations: 8 · (2^20 + 3) workgroups of 512
     threads, more than the 2^32 threads of a launch, so the batch takes two.
