@@ -1469,14 +1469,13 @@ __global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t tile0,
 
 // ------------------------------------------------------ FP16 GEMV control
 // One wavefront per row; lanes stream 16-byte chunks of the row (1 KiB per
-// wavefront load), kHeadChunks of them in flight, the first ones requested
-// before x is staged in LDS; f32 accumulation with v_dot2_f32_f16, chunk after
-// chunk.  Bound by the stream of W; one load in flight a wave left its latency
-// in the open: 128256×4096 171.7 -> 155.8 µs (6.1 -> 6.75 TB/s), 32000×4096
-// 47.3 -> 40.5, 33333×1032 17.0 -> 12.7; eight in flight gain nothing more and
-// lose on short rows (33333×1032 23.5).
-constexpr int kHeadChunks = 4;
-
+// wavefront load), CH of them in flight, the first ones requested before x is
+// staged in LDS; f32 accumulation with v_dot2_f32_f16, chunk after chunk.  Bound
+// by the stream of W; one load in flight a wave, requested after x, left its
+// latency in the open: 128256×4096 171.7 -> 155.8 µs (6.1 -> 6.75 TB/s), 32000×4096
+// 47.3 -> 40.5, 33333×1032 17.0 -> 12.7; eight in flight gain nothing more.
+// AUX: the loads' cache hint, 0 or kStreamed.
+template <int CH, int AUX>
 __global__ __launch_bounds__(512) void fp16_gemv_kernel(const uint16_t* __restrict__ W,
                                                         const uint16_t* __restrict__ x,
                                                         float* __restrict__ y, int64_t M,
@@ -1489,11 +1488,11 @@ __global__ __launch_bounds__(512) void fp16_gemv_kernel(const uint16_t* __restri
   // the row; nothing is read past its end, nor for a wave past the last row
   const __amdgpu_buffer_rsrc_t rw = row < M ? make_rsrc(W + row * K, (uint64_t)K * 2) : null_rsrc();
   auto chunk = [&](int c) {
-    return __builtin_amdgcn_raw_buffer_load_b128(rw, c * 16, 0, kStreamed);
+    return __builtin_amdgcn_raw_buffer_load_b128(rw, c * 16, 0, AUX);
   };
-  u32x4a w[kHeadChunks];
+  u32x4a w[CH];
 #pragma unroll
-  for (int u = 0; u < kHeadChunks; ++u) w[u] = chunk(lane + 64 * u);
+  for (int u = 0; u < CH; ++u) w[u] = chunk(lane + 64 * u);
   for (int k = threadIdx.x; k < K8; k += blockDim.x) xs[k] = ((const u32x4a*)x)[k];
   __syncthreads();
   if (row >= M) return;
@@ -1506,15 +1505,15 @@ __global__ __launch_bounds__(512) void fp16_gemv_kernel(const uint16_t* __restri
     acc = __builtin_amdgcn_fdot2(as_h2(wv.w), as_h2(xv.w), acc, false);
   };
   int c0 = 0;
-  for (; c0 + 64 * kHeadChunks < K8; c0 += 64 * kHeadChunks) {
+  for (; c0 + 64 * CH < K8; c0 += 64 * CH) {
 #pragma unroll
-    for (int u = 0; u < kHeadChunks; ++u) {
+    for (int u = 0; u < CH; ++u) {
       add(w[u], c0 + 64 * u + lane);
-      w[u] = chunk(c0 + 64 * (u + kHeadChunks) + lane);
+      w[u] = chunk(c0 + 64 * (u + CH) + lane);
     }
   }
 #pragma unroll
-  for (int u = 0; u < kHeadChunks; ++u)
+  for (int u = 0; u < CH; ++u)
     if (c0 + 64 * u + lane < K8) add(w[u], c0 + 64 * u + lane);
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
   if (lane == 0) y[row] = acc;
@@ -1740,6 +1739,37 @@ static int launch_decode(const GemvArgs& a, int8_t* z, uint16_t* c, uint8_t* g, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail("decode launch", e);
   }
+  return LEECH_OK;
+}
+
+// The FP16 control's form.  A load past a row's end costs its issue, so a row of
+// one wavefront load takes one in flight and a row of two takes two (µs, in
+// caches: 32000×512 6.4 with one, 7.7 with four; 20000×768 5.8 with two, 6.3 with
+// four; 4096×1536 and longer rows gain from four).  A W of up to 48 MiB may be
+// read again from the caches, where the non-temporal hint loses them; above that
+// the hint gains on first reads and costs little on later ones (µs, read again /
+// from HBM, without and with the hint: 4096×4096 3.9 / 7.6 and 6.6 / 7.3,
+// 20000×1536 (59 MiB) 10.7 / 12.0 and 9.7 / 11.3, 128256×4096 175 / 181 and 155 /
+// 161; short rows never gain: 200000×512 33.7 / 47.4 and 44.4 / 46.6).
+constexpr int64_t kHeadCached = 48ll << 20;
+
+template <int CH, int AUX>
+static int launch_fp16(const uint16_t* W, const uint16_t* x, float* y, int64_t M, int64_t K,
+                       hipStream_t st) {
+  const int waves = 8;
+  const size_t shmem = (size_t)K * 2;
+  const int64_t blocks = (M + waves - 1) / waves;
+  if (blocks > kMaxLaunchThreads / (64 * waves))
+    return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
+  if (shmem > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)fp16_gemv_kernel<CH, AUX>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (e != hipSuccess) return hip_fail("hipFuncSetAttribute", e);
+  }
+  hipLaunchKernelGGL((fp16_gemv_kernel<CH, AUX>), dim3((unsigned)blocks), dim3(64 * waves), shmem,
+                     st, W, x, y, M, K);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail("fp16 gemv launch", e);
   return LEECH_OK;
 }
 
@@ -1972,21 +2002,12 @@ int leech_fp16_gemv_ref(int64_t M, int64_t K, const uint16_t* d_W, const uint16_
   if (M <= 0 || K <= 0 || K % 8) return set_error(LEECH_E_SHAPE, "need M > 0, K > 0, K % 8 == 0");
   if (((uintptr_t)d_W & 15) || ((uintptr_t)d_x & 15))
     return set_error(LEECH_E_ARG, "W and x must be 16-byte aligned");
-  size_t shmem = (size_t)K * 2;
-  if (shmem > 160 * 1024) return set_error(LEECH_E_SHAPE, "K too large for the LDS-staged x");
-  if (shmem > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)fp16_gemv_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return hip_fail("hipFuncSetAttribute", e);
-  }
-  const int waves = 8;
-  if ((M + waves - 1) / waves > kMaxLaunchThreads / (64 * waves))
-    return set_error(LEECH_E_SHAPE, "matrix too large for one launch");
-  hipLaunchKernelGGL(fp16_gemv_kernel, dim3((unsigned)((M + waves - 1) / waves)), dim3(64 * waves),
-                     shmem, (hipStream_t)stream, d_W, d_x, d_y, M, K);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail("fp16 gemv launch", e);
-  return LEECH_OK;
+  if (K > 80 * 1024) return set_error(LEECH_E_SHAPE, "K too large for the LDS-staged x");
+  const hipStream_t st = (hipStream_t)stream;
+  if (K <= 512) return launch_fp16<1, 0>(d_W, d_x, d_y, M, K, st);
+  if (K <= 1024) return launch_fp16<2, 0>(d_W, d_x, d_y, M, K, st);
+  if (M <= kHeadCached / 2 / K) return launch_fp16<4, 0>(d_W, d_x, d_y, M, K, st);
+  return launch_fp16<4, kStreamed>(d_W, d_x, d_y, M, K, st);
 }
 
 int leech_set_exception_mode(int mode) {

@@ -179,6 +179,29 @@ def test_fp16_control_chunks(dev, K):
     assert (np.abs(y - y64) <= bound).all()
 
 
+@pytest.mark.parametrize("M,K", [(9, 8), (9, 512), (9, 520), (17, 1024), (17, 1032), (33, 81920),
+                                 (12288, 2048), (12289, 2048), (33333, 1032)])
+def test_fp16_control_forms(dev, M, K):
+    """The kernel's forms by row length (up to 512, up to 1024, above) and matrix
+    size (up to 48 MiB, above), on both sides of each line, NaN after the last
+    row: one wavefront a row adds chunk after chunk in all of them, so a few
+    rows' copy in a small matrix gives the same bits."""
+    say(f"[fp16 forms] {M}x{K}")
+    g = torch.Generator(device=dev).manual_seed(K)
+    buf = torch.full((M * K + 8 * 64 * 8,), float("nan"), dtype=torch.float16, device=dev)
+    W = buf[:M * K].view(M, K)
+    W.copy_((torch.randn(M, K, generator=g, device=dev) * 0.05).half())
+    x = torch.randn(K, generator=g, device=dev).half()
+    y = P.fp16_gemv(W, x)
+    W64, x64 = W.double(), x.double()
+    # f32 sums of K products: K roundings of at most 2^-24 of the sum of magnitudes
+    bound = K * 2.0 ** -24 * (W64.abs() @ x64.abs())
+    assert bool(((y.double() - W64 @ x64).abs() <= bound).all())
+    rows = [0, M // 2, M - 1]
+    assert torch.equal(P.fp16_gemv(W[rows].contiguous(), x).view(torch.int32),
+                       y[rows].view(torch.int32))
+
+
 @pytest.mark.parametrize("M,K", [(65, 24 * 17), (4096, 4096)])
 def test_noweights_control(dev, dcb, M, K):
     say(f"[noweights] M={M} K={K}")
