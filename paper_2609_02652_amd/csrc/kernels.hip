@@ -1344,18 +1344,117 @@ __global__ __launch_bounds__(kMaxWaves * 64, 4) void gemv_kernel_mx(GemvArgs a) 
 }
 
 // --------------------------------------------------------- decode export
-// Verification decode with the GEMV's decode function and plain loads.  A
-// workgroup takes eight consecutive units of a tile, a wave one unit at a time
-// in storage order, so records are read once and in line and a lane's place
-// needs no division by the matrix's shape.  The binary16 pairs become integer
-// coordinates (|z| in the low byte of each half, the sign in its bit 15),
-// which pass through LDS so that rows leave in runs of 192 bytes and more.
-// Bound by its bytes, 14 read and 27 written a Planes14 block.  A thread a row-major block,
-// with 64-bit divisions and records fetched again for every row that shares
-// their line, took 49.7 µs at 14336×4096 (28.0 now, 3.6 TB/s), 16.4 at
-// 5120×5120 (12.8) and 10.0 at 4096×4096 (9.5); 16 units a workgroup gain at
-// the first (24.9) and lose at 17408×1024 (11.6 against 11.1).
+// Verification decode with the GEMV's decode function and plain loads.  The
+// binary16 pairs become integer coordinates: |z| in the low byte of each half,
+// the sign in its bit 15.
 typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
+// The block at place ul of unit g of a tile of R_t rows: its 24 coordinates
+// and its class | gain << 9.
+template <int LAYOUT>
+__device__ __forceinline__ void decode_place(const GemvArgs& a, int tile, int g, int R_t,
+                                             uint32_t ul, u32x2a zw[3], uint32_t& e) {
+  const GlobalSide side{&a};
+  auto tab = [&](uint32_t e16) -> LdsEntry {
+    return make_entry_as<LAYOUT>(a.table, e16 >> 4, 1.0f, 1.0f);
+  };
+  auto tab14 = [&](uint32_t e16) -> LdsEntry { return make_entry(a.table, e16 >> 4, 1.0f, 1.0f); };
+  auto cw = [&](uint32_t m) -> uint32_t {
+    const uint32_t s = golay_word(a.codewords, m);
+    return g70_place(s, s >> 4);
+  };
+  Pref p = {0, 0, 0, 0, 0, 0, 0, 0};
+  if constexpr (LAYOUT == LEECH_SLOT32) {
+    uint64_t bits;
+    uint32_t base;
+    side.unit_entry(a.side0, tile * (int)a.groups + g, bits, base);
+    const uint32_t nbelow = (uint32_t)__builtin_popcountll(bits & ((1ull << ul) - 1ull));
+    const uint32_t* rec = (const uint32_t*)(a.main + (uint64_t)base * 4) +
+                          (ul * (uint32_t)kSlot32Small +
+                           nbelow * (uint32_t)(kSlot32Large - kSlot32Small)) / 4;
+    const u32x4 w = *(const u32x4*)rec;
+    p.w0 = w.x; p.w1 = w.y; p.w2 = w.z; p.w3 = w.w; p.w4 = rec[4];
+  } else {
+    const uint64_t off =
+        ((uint64_t)tile * a.R * a.nb + (uint64_t)g * (R_t * a.C) + ul) * Stride<LAYOUT>::v;
+    const uint8_t* w = a.main + (off & ~3ull);
+    if constexpr (LAYOUT == LEECH_PLANES14) {
+      const u32x4 v = *(const u32x4*)w;
+      p.w0 = v.x; p.w1 = v.y; p.w2 = v.z; p.w3 = v.w;
+    } else {
+      const u32x3 v = *(const u32x3*)w;
+      p.w0 = v.x; p.w1 = v.y; p.w2 = v.z;
+    }
+    p.sh = (uint32_t)(off & 3u) * 8u;
+    p.esh = (p.sh + 28u) & 31u;
+  }
+  uint32_t h[12], e16;
+  LdsEntry te;
+  decode_block<LAYOUT>(p, tile, tab, tab14, cw, side, h, e16, te);
+  e = e16 >> 4;
+  // each half's magnitude, negated where its sign bit is set: a 16-bit
+  // number whose low byte is the coordinate
+  uint32_t v[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const s16x2 neg = __builtin_bit_cast(s16x2, h[k]) >> (short)15;
+    v[k] = __builtin_bit_cast(uint32_t,
+                              (__builtin_bit_cast(s16x2, h[k] & 0x00FF00FFu) ^ neg) - neg);
+  }
+  // coordinate 4g + r stands in pair 3r + m: g = 0, 1, 2 in low halves (m =
+  // g), 4, 5, 3 in high ones (m = 0, 1, 2)
+  uint32_t z[6];
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    const uint32_t lo = perm(v[3 + m], v[m], 0x06020400u);      // rows 0 and 1
+    const uint32_t hi = perm(v[9 + m], v[6 + m], 0x06020400u);  // rows 2 and 3
+    z[m] = perm(hi, lo, 0x05040100u);
+    z[m < 2 ? 4 + m : 3] = perm(hi, lo, 0x07060302u);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) zw[q] = u32x2a{z[2 * q], z[2 * q + 1]};
+}
+
+// A thread a row-major block, for matrices of fewer than decode_blocks(C)
+// blocks.  All or most of their threads are on the chip at once (2048 on each of
+// 256 CUs), so a launch takes little more than one thread's latency: the
+// divisions, one record, one decode, with no barrier and no hop through LDS.
+template <int LAYOUT>
+__global__ __launch_bounds__(256) void decode_small_kernel(GemvArgs a, uint32_t n, int8_t* zout,
+                                                           uint16_t* cout, uint8_t* gout) {
+  const uint32_t bi = blockIdx.x * 256 + threadIdx.x;
+  if (bi >= n) return;
+  const uint32_t nb = (uint32_t)a.nb, R = (uint32_t)a.R, C = (uint32_t)a.C;
+  const uint32_t r = bi / nb, j = bi - r * nb;
+  const uint32_t tile = r / R, g = j / C;
+  const uint32_t R_t = min(R, (uint32_t)a.M - tile * R), C_g = min(C, nb - g * C);
+  u32x2a zw[3];
+  uint32_t e;
+  decode_place<LAYOUT>(a, (int)tile, (int)g, (int)R_t, (r - tile * R) * C_g + (j - g * C), zw, e);
+  if (zout) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      *(u32x2u*)(zout + bi * (uint32_t)kDim + 8 * q) = u32x2u{zw[q].x, zw[q].y};
+  }
+  if (cout) cout[bi] = (uint16_t)(e & 511u);
+  if (gout) gout[bi] = (uint8_t)(e >> 9);
+}
+
+// Larger matrices: a workgroup takes eight consecutive units of a tile, a wave
+// one unit at a time in storage order, so records are read once and in line and
+// a lane's place needs no division by the matrix's shape; the coordinates pass
+// through LDS so that rows leave in runs of 192 bytes and more.  Bound by its
+// bytes, 14 read and 27 written a Planes14 block.  A thread a block fetches
+// records again for every row that shares their line (µs, here against a thread
+// a block): 14336×4096 (C = 1) 27.9 and 49.0 (3.5 TB/s), 5120×5120 (C = 3) 12.4
+// and 15.7.  Below the lines it is ahead, the further out the shorter the runs
+// here or the longer its own runs of records (C = 1, 28672×1024, 1.2 M blocks:
+// 16.0 and 15.4, from HBM 23.1 and 17.9; C = 16, 1024×17408, 743,424 blocks: 9.2
+// and 7.7; other C, 3584×4096, 612,864 blocks: 8.8 and 7.4; 64×512 2.9 and 2.6).
+constexpr int64_t decode_blocks(int C) {
+  return (C == 1 ? 1200 : C == 16 ? 768 : 640) * 1024;
+}
 constexpr int kDecodeUnits = 8;             // units of a workgroup
 constexpr int kDecodePad = 8;               // bytes after each row's run, against bank conflicts
 
@@ -1373,15 +1472,6 @@ __global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t tile0,
   const int R_t = (int)min((int64_t)a.R, a.M - (int64_t)tile * a.R);
   const int C_last = (int)(a.nb - (int64_t)(groups - 1) * a.C);
   const int lane = threadIdx.x & 63;
-  const GlobalSide side{&a};
-  auto tab = [&](uint32_t e16) -> LdsEntry {
-    return make_entry_as<LAYOUT>(a.table, e16 >> 4, 1.0f, 1.0f);
-  };
-  auto tab14 = [&](uint32_t e16) -> LdsEntry { return make_entry(a.table, e16 >> 4, 1.0f, 1.0f); };
-  auto cw = [&](uint32_t m) -> uint32_t {
-    const uint32_t s = golay_word(a.codewords, m);
-    return g70_place(s, s >> 4);
-  };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int u = wave; u < kDecodeUnits && g0 + u < groups; u += 4) {
     const int g = g0 + u;
@@ -1389,57 +1479,13 @@ __global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t tile0,
     const uint32_t r = (uint32_t)lane * (65536u / (uint32_t)C_g + 1) >> 16;   // lane / C_g
     const uint32_t col = (uint32_t)(u * a.C) + lane - r * C_g;
     if (lane >= R_t * C_g) continue;
-    Pref p = {0, 0, 0, 0, 0, 0, 0, 0};
-    if constexpr (LAYOUT == LEECH_SLOT32) {
-      uint64_t bits;
-      uint32_t base;
-      side.unit_entry(a.side0, tile * groups + g, bits, base);
-      const uint32_t nbelow = (uint32_t)__builtin_popcountll(bits & ((1ull << lane) - 1ull));
-      const uint32_t* rec = (const uint32_t*)(a.main + (uint64_t)base * 4) +
-                            (lane * (uint32_t)kSlot32Small +
-                             nbelow * (uint32_t)(kSlot32Large - kSlot32Small)) / 4;
-      const u32x4 w = *(const u32x4*)rec;
-      p.w0 = w.x; p.w1 = w.y; p.w2 = w.z; p.w3 = w.w; p.w4 = rec[4];
-    } else {
-      const uint64_t off =
-          ((uint64_t)tile * a.R * a.nb + (uint64_t)g * (R_t * a.C) + lane) * Stride<LAYOUT>::v;
-      const uint8_t* w = a.main + (off & ~3ull);
-      if constexpr (LAYOUT == LEECH_PLANES14) {
-        const u32x4 v = *(const u32x4*)w;
-        p.w0 = v.x; p.w1 = v.y; p.w2 = v.z; p.w3 = v.w;
-      } else {
-        const u32x3 v = *(const u32x3*)w;
-        p.w0 = v.x; p.w1 = v.y; p.w2 = v.z;
-      }
-      p.sh = (uint32_t)(off & 3u) * 8u;
-      p.esh = (p.sh + 28u) & 31u;
-    }
-    uint32_t h[12], e16;
-    LdsEntry te;
-    decode_block<LAYOUT>(p, tile, tab, tab14, cw, side, h, e16, te);
-    // each half's magnitude, negated where its sign bit is set: a 16-bit
-    // number whose low byte is the coordinate
-    uint32_t v[12];
+    u32x2a* const zo = (u32x2a*)(zs + r * row_bytes + col * kDim);
+    u32x2a zw[3];
+    uint32_t e;
+    decode_place<LAYOUT>(a, tile, g, R_t, (uint32_t)lane, zw, e);
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      const s16x2 neg = __builtin_bit_cast(s16x2, h[k]) >> (short)15;
-      v[k] = __builtin_bit_cast(
-          uint32_t, (__builtin_bit_cast(s16x2, h[k] & 0x00FF00FFu) ^ neg) - neg);
-    }
-    // coordinate 4g + r stands in pair 3r + m: g = 0, 1, 2 in low halves (m =
-    // g), 4, 5, 3 in high ones (m = 0, 1, 2)
-    u32x2a* zo = (u32x2a*)(zs + r * row_bytes + col * kDim);
-    uint32_t zw[6];
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      const uint32_t lo = perm(v[3 + m], v[m], 0x06020400u);      // rows 0 and 1
-      const uint32_t hi = perm(v[9 + m], v[6 + m], 0x06020400u);  // rows 2 and 3
-      zw[m] = perm(hi, lo, 0x05040100u);
-      zw[m < 2 ? 4 + m : 3] = perm(hi, lo, 0x07060302u);
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) zo[q] = u32x2a{zw[2 * q], zw[2 * q + 1]};
-    es[r * W + col] = (uint16_t)(e16 >> 4);
+    for (int q = 0; q < 3; ++q) zo[q] = zw[q];
+    es[r * W + col] = (uint16_t)e;
   }
   __syncthreads();
   // rows out, the flat index divided by a row's share with a reciprocal that
@@ -1447,7 +1493,6 @@ __global__ __launch_bounds__(256) void decode_kernel(GemvArgs a, uint32_t tile0,
   const uint32_t cols = (uint32_t)min((int64_t)W, a.nb - (int64_t)g0 * a.C);
   const int64_t blk0 = (int64_t)tile * a.R * a.nb + (int64_t)g0 * a.C;
   if (zout) {
-    typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
     const uint32_t n8 = cols * (kDim / 8), inv = (1u << 20) / n8 + 1;
     for (uint32_t i = threadIdx.x; i < R_t * n8; i += 256) {
       const uint32_t r = i * inv >> 20, k = i - r * n8;
@@ -1727,6 +1772,14 @@ static int launch_batch_mx(const GemvArgs& a, hipStream_t st) {
 
 template <int LAYOUT>
 static int launch_decode(const GemvArgs& a, int8_t* z, uint16_t* c, uint8_t* g, hipStream_t st) {
+  if (a.M * a.nb < decode_blocks(a.C)) {      // (at most 2^31 · 2^24)
+    const uint32_t n = (uint32_t)(a.M * a.nb);
+    hipLaunchKernelGGL(decode_small_kernel<LAYOUT>, dim3((n + 255) / 256), dim3(256), 0, st, a, n,
+                       z, c, g);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail("decode launch", e);
+    return LEECH_OK;
+  }
   const int64_t chunks = (a.groups + kDecodeUnits - 1) / kDecodeUnits;
   const int W = kDecodeUnits * a.C;
   const size_t shmem = (size_t)a.R * (W * kDim + kDecodePad + W * sizeof(uint16_t));

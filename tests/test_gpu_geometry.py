@@ -190,6 +190,42 @@ def test_decode_runs(dev, dcb, geo, step):
     assert np.array_equal(g[:-1].reshape(M, nb), inp.gain) and g[-1] == 9
 
 
+@pytest.mark.parametrize("geo,step", [((1, 64), -1), ((1, 64), 1), ((3, 20), -1), ((3, 20), 1),
+                                      ((4, 16), 0), ((16, 4), -1), ((16, 4), 1)])
+@pytest.mark.parametrize("layout", [P.SLOT32, P.PLANES14, P.PLANES12X, P.GOLAY70])
+def test_decode_both_kernels(dev, dcb, layout, geo, step):
+    """Decode on both sides of the block count that chooses the kernel:
+    rows of one block fewer than a workgroup's eight units, as many and one more,
+    a ragged last tile, z at an address that is a multiple of 4 only, nothing
+    written past an output."""
+    (C, R), pool = geo, 4099
+    nb = 8 * C + step
+    inp = synth.make_gemv_inputs(pool, 24, seed=3, name="decode-both")
+    cls, sm, lv = dcb.cb.fields_from_points(inp.z[:, 0])
+    line = {1: 1200, 16: 768}.get(C, 640) * 1024
+    over = -(-line // nb)
+    for M in ((line - 1) // nb, over + (over % R == 0)):
+        say(f"[decode both] layout {layout} {geo} {M}x{24 * nb}")
+        at = np.random.default_rng(nb).integers(0, pool, (M, nb))
+        gain = inp.gain[at, 0]
+        mat = P.LeechMatrix.from_fields(dcb, layout, cls[at], gain, sm[at], lv[at],
+                                        np.ones((M, nb), np.float16), dev, geometry=geo)
+        n = M * nb
+        z = torch.full((24 * n + 8,), 99, dtype=torch.int8, device=dev)
+        c = torch.full((n + 1,), 999, dtype=torch.int16, device=dev)
+        g = torch.full((n + 1,), 9, dtype=torch.uint8, device=dev)
+        m, s0, s1 = mat._ptrs()
+        _lib.decode_blocks(mat.desc, m, s0, s1, dcb.table.data_ptr(), dcb.golay_gen.data_ptr(),
+                           z.data_ptr() + 4, c.data_ptr(), g.data_ptr(),
+                           torch.cuda.current_stream().cuda_stream)
+        where = torch.from_numpy(at.reshape(-1)).to(dev)
+        assert torch.equal(z[4:-4].view(n, 24), torch.from_numpy(inp.z[:, 0]).to(dev)[where])
+        assert torch.equal(c[:-1], torch.from_numpy(cls.astype(np.int16)).to(dev)[where])
+        assert torch.equal(g[:-1], torch.from_numpy(inp.gain[:, 0].copy()).to(dev)[where])
+        assert bool((z[:4] == 99).all()) and bool((z[-4:] == 99).all())
+        assert int(c[-1]) == 999 and int(g[-1]) == 9
+
+
 def test_decode_past_one_launch(dev, dcb):
     """2^26 + 5 rows of one block in tiles of four: 2^24 + 2 workgroups of 256
     threads, more than the 2^32 threads of a launch, so the decode takes two.
