@@ -779,7 +779,7 @@ __host__ __device__ constexpr bool red_in_x(int nb_vectors, int xblocks, int wav
 // NB: batch width (1, 2, 4, 8 or 16).  Each decoded block is multiplied with
 // NB activations (NB > 1: Planes14), in the same order as a single GEMV, so
 // every output vector is bit-identical to that activation's own GEMV.
-// MX (NB > 1): the products go through the matrix cores instead, as the
+// MX (NB ≤ 8): the products go through the matrix cores instead, as the
 // 16-block 4×4×4 binary16 MFMA with f32 accumulation.  Lanes are placed by
 // column (lane c·R + r holds block (r, c) of the unit, R = tile_rows, a
 // multiple of 4), so each block of 4 lanes holds blocks of one column.  In
@@ -807,7 +807,7 @@ __host__ __device__ constexpr bool red_in_x(int nb_vectors, int xblocks, int wav
 // the plain launch's.
 template <int LAYOUT, bool EVEN, int NB, int XPER, bool ROT, int PRO, bool PHASE, bool MX>
 __device__ __forceinline__ void gemv_body(const GemvArgs& a) {
-  static_assert(!MX || (NB > 1 && LAYOUT == LEECH_PLANES14 && !ROT && !PHASE),
+  static_assert(!MX || (NB <= 8 && LAYOUT == LEECH_PLANES14 && !ROT && !PHASE),
                 "matrix-core products serve batched Planes14 launches");
   constexpr int kPrefetch = pro_prefetch(PRO);        // units in flight per wave
   constexpr int kFirstUnits = pro_first(PRO);         // of them, before the barrier
@@ -1335,11 +1335,12 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemv_kernel(GemvArgs a) {
   gemv_body<LAYOUT, EVEN, NB, XPER, ROT, PRO, PHASE, false>(a);
 }
 
-// Matrix-core batches of 2 and 4 activations (wider ones: batch.hip): held to
-// 128 registers (four waves per SIMD), so that two 8-wave workgroups share a CU
-// when there are more tiles than CUs.
+// Matrix-core batches in narrow launches (see narrow_batch).  Up to four
+// activations: held to 128 registers (four waves per SIMD), so that two 8-wave
+// workgroups share a CU when there are more tiles than CUs.  Eight would spill
+// there, and their staged activations mostly leave LDS for one workgroup a CU.
 template <int LAYOUT, bool EVEN, int NB, int XPER>
-__global__ __launch_bounds__(kMaxWaves * 64, 4) void gemv_kernel_mx(GemvArgs a) {
+__global__ __launch_bounds__(kMaxWaves * 64, NB <= 4 ? 4 : 2) void gemv_kernel_mx(GemvArgs a) {
   gemv_body<LAYOUT, EVEN, NB, XPER, false, 0, false, true>(a);
 }
 
@@ -1690,9 +1691,10 @@ static int launch_gemv_pro(const GemvArgs& a, size_t shmem, hipStream_t st) {
 template <int LAYOUT, bool EVEN, int NB = 1, bool PHASE = false, bool MX = false>
 static int launch_gemv_as(const GemvArgs& a, size_t shmem, hipStream_t st) {
   // one activation block per thread when the workgroup's threads cover them
-  if (NB > 1 || a.groups * a.C <= 64 * a.waves)
-    return launch_gemv_pro<LAYOUT, EVEN, NB, 1, PHASE, MX>(a, shmem, st);
-  return launch_gemv_pro<LAYOUT, EVEN, NB, 2, PHASE, MX>(a, shmem, st);
+  if constexpr (NB == 1)
+    if (a.groups * a.C > 64 * a.waves)
+      return launch_gemv_pro<LAYOUT, EVEN, NB, 2, PHASE, MX>(a, shmem, st);
+  return launch_gemv_pro<LAYOUT, EVEN, NB, 1, PHASE, MX>(a, shmem, st);
 }
 
 template <int LAYOUT, int NB = 1, bool PHASE = false, bool MX = false>
@@ -1753,21 +1755,69 @@ static int batch_width(const GemvArgs& a, int left) {
 // activation.
 static std::atomic<int> g_batch_mode{LEECH_BATCH_AUTO};
 
-// A matrix-core batch: up to four activations that fit in LDS beside the class
-// table in one gemv_kernel_mx launch, whose steps read whole units and have no
-// idle activation rows; everything else through batch.hip's kernel.  (Both
-// give the same bits.)
+// Matrix-core batches go through one of two kernels, which give the same bits.
+// gemv_kernel_mx (narrow launches of 1, 2, 4 or 8) reads whole units in a step and
+// has no idle activation rows, but stages all its activations before it starts.
+// batch.hip's kernel takes any batch in one launch and 16 activations a tile, but
+// its steps hold RW rows × 64 / RW columns: with 16-row tiles of the 4-row
+// geometries a wave makes four times the steps.
+//
+// Narrow: up to two or four activations that fit, in one launch.  Beyond that
+// for the geometries of few rows, from the number of columns at which as many
+// narrow launches as the batch takes are ahead of the one (µs, narrow and wide,
+// 256 to 1024 rows in 16 × 4 unless noted): 8 activations, K = 4096 7.3 and 6.7,
+// 5120 7.7 and 8.0, 8192 8.7 and 10.1; 8 × 8 6144 8.3 and 7.8, 8192 8.6 and 9.1; 3 ×
+// 20, 5120 rows, 2048 6.9 and 6.4, 3072 7.7 and 7.8, 5120 9.6 and 10.3, 9120 12.4
+// and 15.2.  Two launches, 13824 14.0 and 12.7, 17408 15.3 and 16.6, 36000 18.4 and
+// 29.0; 8 × 8 20480 17.3 and 17.3, 36000 23.3 and 27.3.  Three, 30000 25.2 and 24.9,
+// 36000 27.0 and 29.0; four single ones, 40000 27.9 and 30.3.  Only where the CUs
+// get no more narrow workgroups each than wide ones: 3 × 20, 7680 rows, 5120
+// columns, 17.5 and 10.7.
+static int narrow_width(const GemvArgs& a, int left) {
+  auto fits = [](size_t bytes) { return bytes <= 160 * 1024; };
+  if (left > 4 && fits(gemv_lds_bytes<LEECH_PLANES14, 8>(a))) return 8;
+  if (left > 2 && fits(gemv_lds_bytes<LEECH_PLANES14, 4>(a))) return 4;
+  return left > 1 && fits(gemv_lds_bytes<LEECH_PLANES14, 2>(a)) ? 2 : 1;
+}
+static bool narrow_batch(const GemvArgs& a) {
+  if (a.nbatch > 8) return false;
+  int launches = 0;
+  for (int left = a.nbatch; left > 0; ++launches) left -= narrow_width(a, left);
+  if (launches == 1 && a.nbatch <= 4) return true;
+  constexpr int64_t never = INT64_MAX;
+  const int64_t from16[] = {200, 700, 1400, 1537}, from8[] = {320, 870, never, never};
+  if (launches > 4) return false;
+  const int64_t from = a.C == 16  ? from16[launches - 1]
+                       : a.C == 8 ? from8[launches - 1]
+                       : a.C == 3 && launches == 1 ? 120 : never;
+  const int64_t cus = 256, rows = a.C == 3 ? 32 : 16;      // of a wide workgroup
+  const int64_t wide = (a.M + rows - 1) / rows;
+  return a.nb >= from && (a.tiles + cus - 1) / cus <= (wide + cus - 1) / cus;
+}
+
 static int launch_batch_mx(const GemvArgs& a, hipStream_t st) {
-  if (a.nbatch <= 2 && gemv_lds_bytes<LEECH_PLANES14, 2>(a) <= 160 * 1024)
-    return launch_gemv<LEECH_PLANES14, 2, false, true>(a, st);
-  if (a.nbatch <= 4 && gemv_lds_bytes<LEECH_PLANES14, 4>(a) <= 160 * 1024)
-    return launch_gemv<LEECH_PLANES14, 4, false, true>(a, st);
   // the activation lengths that the single GEMV serves
   if (gemv_lds_bytes<LEECH_PLANES14>(a) > 160 * 1024)
     return set_error(LEECH_E_SHAPE, "Kpad too large for the LDS-staged activation");
-  const BatchCall c = {a.main, a.table, a.scale, a.x,   a.y,   a.cen0, a.cen1, a.main_bytes,
-                       a.M,    a.nb,    a.ldx,   a.ldy, a.C, a.R,    a.nbatch};
-  return launch_batch_mfma(c, st);
+  if (!narrow_batch(a)) {
+    const BatchCall c = {a.main, a.table, a.scale, a.x,   a.y,   a.cen0, a.cen1, a.main_bytes,
+                         a.M,    a.nb,    a.ldx,   a.ldy, a.C, a.R,    a.nbatch};
+    return launch_batch_mfma(c, st);
+  }
+  for (int b0 = 0; b0 < a.nbatch;) {
+    GemvArgs c = a;
+    const int w = narrow_width(a, a.nbatch - b0);
+    c.x = a.x + (int64_t)b0 * a.ldx;
+    c.y = a.y + (int64_t)b0 * a.ldy;
+    c.nbatch = std::min(w, a.nbatch - b0);
+    const int rc = w == 8   ? launch_gemv<LEECH_PLANES14, 8, false, true>(c, st)
+                   : w == 4 ? launch_gemv<LEECH_PLANES14, 4, false, true>(c, st)
+                   : w == 2 ? launch_gemv<LEECH_PLANES14, 2, false, true>(c, st)
+                            : launch_gemv<LEECH_PLANES14, 1, false, true>(c, st);
+    if (rc) return rc;
+    b0 += c.nbatch;
+  }
+  return LEECH_OK;
 }
 
 template <int LAYOUT>

@@ -204,6 +204,35 @@ def test_wide_batch_tiles(dev, dcb, geo, M, K, B):
     assert torch.all(Y[:, M] == -3.0)
 
 
+# both sides of the lines between narrow launches and the wide kernel: one launch
+# of 8, two of 4, three of 2, single ones, by lane_cols
+NARROW_CASES = [((16, 4), 199, (5, 8)), ((16, 4), 200, (5, 8)), ((16, 4), 699, (5, 8)),
+                ((16, 4), 700, (5, 7, 8)), ((16, 4), 1001, (3, 4)), ((16, 4), 1399, (5, 6)),
+                ((16, 4), 1400, (5, 6)), ((16, 4), 1536, (2, 4)), ((16, 4), 1537, (2, 3, 4, 5)),
+                ((16, 4), 3019, (2, 4)), ((8, 8), 319, (6,)), ((8, 8), 320, (5, 6, 8)),
+                ((8, 8), 869, (3,)), ((8, 8), 870, (3, 4)), ((8, 8), 1601, (2, 3)),
+                ((3, 20), 119, (7,)), ((3, 20), 120, (5, 7, 8)), ((3, 20), 384, (8,)),
+                ((3, 20), 386, (8,)), ((1, 64), 400, (5, 8)), ((4, 16), 385, (5, 8))]
+
+
+@pytest.mark.parametrize("geo,nb,batches", NARROW_CASES)
+def test_narrow_and_wide_batches(dev, dcb, geo, nb, batches):
+    """A batch's bits do not depend on the kernel: those of a batch of 16, which
+    is always the wide one's, with a ragged last tile, strided activations and
+    outputs, and nothing written past an output row."""
+    M = geo[1] + 5
+    say(f"[narrow] {geo} {M}x{24 * nb} B={batches}")
+    inp, mat = build(dev, dcb, M, 24 * nb, nb, geometry=geo)
+    g = torch.Generator().manual_seed(nb)
+    X = torch.randn(16, inp.Kpad + 8, generator=g).half().to(dev)[:, :inp.Kpad]
+    want = mat.gemv_batch(X, centroids=CEN)
+    for B in batches:
+        Y = torch.full((B + 1, M + 3), -3.0, dtype=torch.float32, device=dev)
+        mat.gemv_batch(X[:B], Y[:B, :M], centroids=CEN)
+        assert torch.equal(Y[:B, :M].view(torch.int32), want[:B].view(torch.int32)), B
+        assert bool((Y[:, M:] == -3.0).all()) and bool((Y[B] == -3.0).all())
+
+
 @pytest.mark.parametrize("geo", [(1, 64), (2, 32), (3, 20), (4, 16), (8, 8), (16, 4)])
 def test_batch_unused_centroid(dev, dcb, geo):
     """No block has gain bit 0, so its centroid does not matter, NaN included:
