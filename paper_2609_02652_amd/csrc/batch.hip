@@ -278,14 +278,20 @@ __global__ __launch_bounds__(kThreads, WPS) void batch_kernel(BatchArgs a) {
       const uint32_t nl = (uint32_t)(n + p), k = nl / C;
       const uint32_t g = (uint32_t)wave + kWaves * k, j = g * C + (nl - k * C);
       const uint32_t idx = __umul24(g, lane_group) + lane_row + j - ((int)g == glast ? lane_skip : 0u);
-      // Past the last column: the buffer's first record, with a scale of zero
-      // and zero activations.  (A record of zeros would bring in class 0's
-      // factor, whose centroid may be one that no block of the matrix has: not
-      // finite, it would turn the zero into a NaN.)  Past the wave's last step
-      // nothing is read, nor used.
+      // Past the last column: a scale of zero, zero activations, and a record of
+      // zeros, which nothing is read for (so the class factors have to be
+      // finite, see launch_batch_mx), or with three columns a unit the buffer's
+      // first record: its tiles take the general path for every step, and the
+      // 32 × 16 one spills four registers with the other choice (5120×17408, 16
+      // activations: 24.7 µs here, 27.5; the other widths lose 2–5% this way).
       const bool live = (int)j < nb;
-      const uint32_t off = live ? __umul24(idx, (uint32_t)kPlanes14Bytes) : 0u;
-      vo = step < steps ? off & ~3u : kOutOfRange;
+      uint32_t off = __umul24(idx, (uint32_t)kPlanes14Bytes);
+      if constexpr (C == 3) {
+        off = live ? off : 0u;
+        vo = step < steps ? off & ~3u : kOutOfRange;
+      } else {
+        vo = live ? off & ~3u : kOutOfRange;
+      }
       s.sh = (off & 2u) << 3;
       vs = live ? idx * 2u : kOutOfRange;
       so = ss = 0;

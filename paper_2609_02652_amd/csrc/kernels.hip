@@ -1773,6 +1773,11 @@ static std::atomic<int> g_batch_mode{LEECH_BATCH_AUTO};
 // 36000 27.0 and 29.0; four single ones, 40000 27.9 and 30.3.  Only where the CUs
 // get no more narrow workgroups each than wide ones: 3 × 20, 7680 rows, 5120
 // columns, 17.5 and 10.7.
+//
+// A centroid that is not finite, or whose class factors would not be, goes
+// through narrow launches whatever the batch: the wide kernel's lanes past the
+// last column multiply a zero by class 0's factor, which may be one that no
+// block of the matrix has.
 static int narrow_width(const GemvArgs& a, int left) {
   auto fits = [](size_t bytes) { return bytes <= 160 * 1024; };
   if (left > 4 && fits(gemv_lds_bytes<LEECH_PLANES14, 8>(a))) return 8;
@@ -1780,6 +1785,7 @@ static int narrow_width(const GemvArgs& a, int left) {
   return left > 1 && fits(gemv_lds_bytes<LEECH_PLANES14, 2>(a)) ? 2 : 1;
 }
 static bool narrow_batch(const GemvArgs& a) {
+  if (!(std::fabs(a.cen0) <= 1e30f && std::fabs(a.cen1) <= 1e30f)) return true;
   if (a.nbatch > 8) return false;
   int launches = 0;
   for (int left = a.nbatch; left > 0; ++launches) left -= narrow_width(a, left);

@@ -248,8 +248,9 @@ def test_batch_unused_centroid(dev, dcb, geo):
     X = torch.from_numpy(activations(24 * nb, 33, seed=nb)).to(dev)
     for B in (2, 4, 5, 16, 33):
         want = mat.gemv_batch(X[:B], centroids=(1.0, 1.25))
-        got = mat.gemv_batch(X[:B], centroids=(float("nan"), 1.25))
-        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), B
+        for unused in (float("nan"), float("inf"), 3e38):
+            got = mat.gemv_batch(X[:B], centroids=(unused, 1.25))
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32)), (B, unused)
 
 
 def test_batch_past_one_launch(dev, dcb):
