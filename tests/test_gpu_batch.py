@@ -6,6 +6,8 @@ GEMV, and bit-identical whatever the batch size and its position in the
 batch.  Batches not a power of two, above 16, wide K (narrower chunks), every
 geometry the matrix-core path takes (ragged tiles, lanes without a column),
 strided activations and outputs."""
+import os
+import re
 import sys
 
 import numpy as np
@@ -200,6 +202,95 @@ def test_wide_batch_tiles(dev, dcb, geo, M, K, B):
         n = min(4, B - b)
         x = X[b:b + n, :inp.Kpad] if n > 1 else X[b - 1:b + 1, :inp.Kpad]
         ref[b:b + n] = mat.gemv_batch(x, centroids=CEN)[-n:]
+    assert torch.equal(Y[:, :M].view(torch.int32), ref.view(torch.int32))
+    assert torch.all(Y[:, M] == -3.0)
+
+
+# (rows, activations, ring depth) of the wide kernel's tiles by lane_cols, widest
+# first, as batch.hip's kTiles and its launch table
+WIDE_TILES = {1: [(64, 64, 4), (64, 32, 4), (64, 16, 4), (32, 16, 4)],
+              2: [(64, 32, 4), (32, 32, 4), (32, 16, 4)],
+              3: [(64, 32, 3), (32, 32, 3), (32, 16, 3)],
+              4: [(64, 32, 4), (32, 32, 4), (32, 16, 4), (16, 16, 4)],
+              8: [(32, 32, 4), (32, 16, 4), (16, 16, 4)],
+              16: [(32, 16, 8), (16, 16, 4)]}
+
+
+def wide_tile(C, M, B):
+    """batch.hip's choose_tile."""
+    for tile in WIDE_TILES[C]:
+        rw, nb = tile[:2]
+        if (nb == 16 or 2 * B > nb) and -(-M // rw) * -(-B // nb) >= 160:
+            break
+    return tile
+
+
+def plain_waves(geo, M, nb, tile):
+    """(row block, wave) pairs whose steps take the steady loop of constant
+    addresses (batch.hip's `plain` with two rings of steps and more), of all."""
+    (C, R), (rw, _, D) = geo, tile
+    sc, groups, plain, pairs = 64 // rw, -(-nb // C), 0, 0
+    for row0 in range(0, M, rw):
+        tile0 = row0 // R
+        t_last = (min(row0 + rw, M) - 1 - tile0 * R) // R
+        for wave in range(min(8, groups)):
+            units = (groups - 1 - wave) // 8 + 1
+            steps = -(-units * C // sc)
+            assert steps >= 3 * D + 1, (geo, tile, wave, steps)
+            pairs += 1
+            plain += ((C % sc == 0 or sc % C == 0) and units * C % sc == 0
+                      and (t_last == 0 or (tile0 + t_last + 1) * R <= M)
+                      and (nb % C == 0 or (groups - 1) % 8 != wave))
+    return plain, pairs
+
+
+def test_wide_tiles_are_the_sources():
+    """WIDE_TILES is what the library compiles."""
+    with open(os.path.join(os.path.dirname(P.__file__), "csrc", "batch.hip")) as f:
+        src = f.read()
+    built = {tuple(map(int, t)) for t in re.findall(r"launch_tile<(\d+), (\d+), (\d+), (\d+), \d+>", src)}
+    assert built == {(C, *t) for C, tiles in WIDE_TILES.items() for t in tiles}
+    for C, tiles in re.findall(r"\{(\d+), \{([\d, ]+)\}\}", src[src.index("kTiles[] ="):]):
+        order = [divmod(int(t), 100) for t in tiles.split(",") if int(t)]
+        assert order == [t[:2] for t in WIDE_TILES[int(C)]], C
+
+
+# per tile: geometry, blocks a row (three rings of steps and more on every
+# wave), rows (full tiles and a ragged last one of an odd number of rows)
+STEADY_CASES = [((1, 64), 107, 353, 0), ((1, 64), 107, 353, 1), ((1, 64), 107, 353, 2),
+                ((1, 48), 211, 203, 3), ((2, 32), 117, 353, 0), ((2, 28), 117, 333, 0),
+                ((2, 32), 213, 353, 1), ((2, 24), 214, 203, 2), ((3, 20), 104, 353, 0),
+                ((3, 16), 104, 331, 0), ((3, 20), 176, 353, 1), ((3, 12), 176, 203, 2),
+                ((4, 16), 139, 353, 0), ((4, 16), 235, 353, 1), ((4, 12), 236, 203, 2),
+                ((4, 16), 427, 203, 3), ((8, 8), 279, 203, 0), ((8, 8), 280, 203, 1),
+                ((8, 4), 471, 107, 2), ((16, 4), 559, 203, 0), ((16, 4), 560, 107, 1)]
+
+
+@pytest.mark.parametrize("geo,nb,M,which", STEADY_CASES)
+def test_wide_batch_steady_loop(dev, dcb, geo, nb, M, which):
+    """Every tile of the wide kernel over rows long enough that each wave refills
+    its ring of records at least twice: the steady loop of constant addresses
+    (record parity included: odd units of one and three columns in the ragged
+    tile), its hand-over to the general one, row blocks and waves that take the
+    general one alone.  The bits of the four-activation launches."""
+    tile = WIDE_TILES[geo[0]][which]
+    B = next(b for b in range(9, 6000) if b % 16 in (3, 11) and wide_tile(geo[0], M, b) == tile)
+    plain, pairs = plain_waves(geo, M, nb, tile)
+    say(f"[batch steady] {geo} {M}x{24 * nb} B={B} tile {tile} plain {plain}/{pairs}")
+    sc = 64 // tile[0]
+    if geo[0] % sc == 0 or sc % geo[0] == 0:
+        assert 0 < plain
+    else:
+        assert plain == 0
+    inp, mat = build(dev, dcb, M, 24 * nb, nb, geometry=geo)
+    g = torch.Generator().manual_seed(B)
+    X = torch.randn(B, inp.Kpad, generator=g).half().to(dev)
+    Y = torch.full((B, M + 1), -3.0, dtype=torch.float32, device=dev)
+    mat.gemv_batch(X, Y[:, :M], centroids=CEN)
+    ref = torch.empty((B, M), dtype=torch.float32, device=dev)
+    for b in range(0, B, 4):
+        b = min(b, B - 4)
+        ref[b:b + 4] = mat.gemv_batch(X[b:b + 4], centroids=CEN)
     assert torch.equal(Y[:, :M].view(torch.int32), ref.view(torch.int32))
     assert torch.all(Y[:, M] == -3.0)
 
