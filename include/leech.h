@@ -306,9 +306,10 @@ int leech_gemv(const leech_layout_desc* desc, const void* d_main, const void* d_
 /* Batched GEMV (§6 "Batching": one decode of each weight serves several
  * activations): Y[b] = W X[b] for b < batch, X[b] binary16 [Kpad] at
  * d_X + b·ldx, Y[b] f32 [M] at d_Y + b·ldy.  Products as
- * leech_set_batch_mode selects.  On the matrix cores (the default) a batch is
- * one launch, which decodes each block once per tile of up to 64 activations;
- * Y[b][r] is within rounding of leech_gemv on X[b] (tested within 2^-15 ·
+ * leech_set_batch_mode selects.  On the matrix cores (the default) each block
+ * is decoded once per tile of up to 64 activations, in one launch (up to eight
+ * activations: one launch or a few, by shape; more than one, too, past a launch's
+ * 2^32 threads); Y[b][r] is within rounding of leech_gemv on X[b] (tested within 2^-15 ·
  * Σ_j |W_rj · X[b]_j|).  With v_dot2 a launch takes up to 16 activations staged
  * in LDS (fewer where Kpad leaves too little: 16 fit up to about Kpad = 4,600,
  * 8 up to about 9,200, the exact bound depending on the column groups'

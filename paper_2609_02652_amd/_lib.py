@@ -358,8 +358,8 @@ BATCH_AUTO, BATCH_DOT2 = 0, 1
 
 def set_batch_mode(mode: int) -> None:
     """Process-wide: the products of batched GEMVs enqueued afterwards
-    (BATCH_AUTO: the matrix cores, 16-block 4x4x4 MFMAs; BATCH_DOT2: v_dot2,
-    bit-identical to single GEMVs)."""
+    (BATCH_AUTO: the matrix cores, 4x4x4, 16x16x4 or 32x32x4 MFMAs, which round
+    alike; BATCH_DOT2: v_dot2, bit-identical to single GEMVs)."""
     check(lib.leech_set_batch_mode(mode))
 
 

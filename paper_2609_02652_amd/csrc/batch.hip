@@ -1,7 +1,7 @@
-// Batched GEMV on the matrix cores for gfx950, for batches of more than the
-// four activations that gemv_kernel_mx takes in one launch: Y[b] = W X[b] with W
-// in the Planes14 layout (§6 "Batching": one decode of each weight serves
-// several activations).
+// Batched GEMV on the matrix cores for gfx950, for the batches that the narrow
+// launches of gemv_kernel_mx do not take (narrow_batch in kernels.hip: up to four
+// activations, up to eight in some shapes): Y[b] = W X[b] with W in the Planes14
+// layout (§6 "Batching": one decode of each weight serves several activations).
 //
 // Arithmetic.  A block's 24 decoded weights meet an activation in six chained
 // binary16 MFMAs of four products each, with an f32 result per (row,
@@ -118,8 +118,10 @@ __device__ __forceinline__ void products(const Acts& x, const uint32_t h[12], f3
 #undef LEECH_CHAIN
 
 // Activation columns staged at a time (whole units, or a whole part of one),
-// and the LDS bytes of one activation's share of them: 16 bytes of padding put
-// 16 consecutive activations' 16-byte reads on distinct banks.
+// and the LDS bytes of one activation's share of them: 16 bytes of padding make it
+// an odd number of 16-byte words, which puts 16 consecutive activations' 16-byte
+// reads on distinct banks.  (With three columns a stage, C = 3 with 64 rows, it is
+// 10 words, and such reads conflict two ways.)
 __host__ __device__ constexpr int x_cols(int C, int RW, int NB) {
   return C == 3 ? (RW == 64 ? 3 : 6) : NB > 32 ? 2 : 4;
 }
@@ -504,8 +506,10 @@ constexpr Tiles kTiles[] = {{1, {6464, 6432, 6416, 3216}}, {2, {6432, 3232, 3216
                             {3, {6432, 3232, 3216, 0}},    {4, {6432, 3232, 3216, 1616}},
                             {8, {3232, 3216, 1616, 0}},    {16, {3216, 1616, 0, 0}}};
 
-// The widest tile that more than half of the batch fills and that makes at
-// least 160 workgroups for the 256 CUs, else the narrowest.  Measured (µs a
+// The widest tile that makes at least 160 workgroups for the 256 CUs, wider than
+// 16 activations only where the batch is more than half as wide, else the
+// narrowest.  (What the batch's last tile holds beside that does not count: 65
+// activations may take two 64-wide tiles.)  Measured (µs a
 // launch, 160 and more workgroups against fewer): 4096×4104 (4 × 16), 16
 // activations: 16 rows 8.0, 32 rows (128 workgroups) 9.1; 32: 32 × 16 9.5, 32 ×
 // 32 (128) 12.2; 64: 32 × 32 13.1, 64 × 32 (128) 17.5; 128: 64 × 32 18.8, 32 × 32

@@ -21,7 +21,9 @@ typedef float f32x4a __attribute__((ext_vector_type(4)));
 constexpr float kTwo24 = 16777216.0f;
 constexpr int kTableBytes = 1024 * 16;    // LDS class-table entries (class | gain << 9)
 // Raw buffer descriptor, word 3, for the gfx9 family (32-bit elements, no
-// swizzle); loads carry the non-temporal hint: records and scales are read once.
+// swizzle), and the non-temporal hint of the GEMV's record and scale loads, which
+// it reads once (the wide batched kernel, which reads them once a batch tile,
+// loads without it).
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kStreamed = 2;
 

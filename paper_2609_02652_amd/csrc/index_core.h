@@ -71,7 +71,7 @@ __host__ __device__ inline uint32_t idx_deposit(uint32_t s, uint32_t mask) {
 }
 
 // the bits of v at the set bits of mask, packed (lowest first)
-__host__ __device__ inline uint32_t idx_extract(uint32_t v, uint32_t mask) {
+inline uint32_t idx_extract(uint32_t v, uint32_t mask) {
   uint32_t out = 0;
   for (int j = 0; mask; ++j) {
     const uint32_t low = mask & (0u - mask);
@@ -83,9 +83,8 @@ __host__ __device__ inline uint32_t idx_extract(uint32_t v, uint32_t mask) {
 
 // q = a / d and a − q·d for a < 2^48 and 0 < d < 2^48: both convert to double
 // exactly, the rounded quotient is within one of the true one, and one integer
-// correction in each direction makes it exact.  (A 64-bit integer division is
-// a long instruction sequence on the GPU; this is a handful.)
-__host__ __device__ inline uint64_t idx_divmod(uint64_t a, uint64_t d, uint64_t* rem) {
+// correction in each direction makes it exact.
+inline uint64_t idx_divmod(uint64_t a, uint64_t d, uint64_t* rem) {
   uint64_t q = (uint64_t)((double)a / (double)d);
   if (q * d > a) --q;
   else if (a - q * d >= d) ++q;
@@ -93,7 +92,7 @@ __host__ __device__ inline uint64_t idx_divmod(uint64_t a, uint64_t d, uint64_t*
   return q;
 }
 
-__host__ __device__ inline int idx_find_class(const IdxTable& T, uint64_t idx) {
+inline int idx_find_class(const IdxTable& T, uint64_t idx) {
   int lo = 0, hi = (int)T.n_classes - 1;     // largest c with offset(c) ≤ idx
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -108,7 +107,7 @@ __host__ __device__ inline int idx_find_class(const IdxTable& T, uint64_t idx) {
 // planes[b]), into `zero` if its magnitude is 0 and into `mag3` if it is
 // ≡ 3 (mod 4).  Loops run over the five level slots so that every array index
 // is a constant.
-__host__ __device__ inline void idx_place(const IdxTable& T, const IdxClass& c, uint32_t on,
+inline void idx_place(const IdxTable& T, const IdxClass& c, uint32_t on,
                                           uint32_t pos, uint64_t a, uint32_t planes[3],
                                           uint32_t* zero, uint32_t* mag3) {
   on &= (1u << c.n_levels) - 1;
@@ -166,7 +165,7 @@ __host__ __device__ inline void idx_place(const IdxTable& T, const IdxClass& c, 
 }
 
 // Rank of the arrangement of the levels in `on` over the positions in `pos`.
-__host__ __device__ inline uint64_t idx_rank(const IdxTable& T, const IdxClass& c, uint32_t on,
+inline uint64_t idx_rank(const IdxTable& T, const IdxClass& c, uint32_t on,
                                              uint32_t pos, const uint8_t* level) {
   uint64_t a = 0;
   uint32_t free = pos;
@@ -194,7 +193,7 @@ __host__ __device__ inline uint64_t idx_rank(const IdxTable& T, const IdxClass& 
 // Decoded fields of a 48-bit code as the three level-code planes (bit i of
 // planes[b] = bit b of coordinate i's level + 1) and the sign mask; false if
 // the code is not one (bits above 47 set, or an index ≥ N).
-__host__ __device__ inline bool idx_decode(const IdxTable& T, uint64_t code, uint16_t* cls,
+inline bool idx_decode(const IdxTable& T, uint64_t code, uint16_t* cls,
                                            uint8_t* gain, uint32_t* smask, uint32_t planes[3]) {
   if (code >> 48) return false;
   const uint64_t idx = code & kIndexMask;
@@ -238,7 +237,7 @@ __host__ __device__ inline bool idx_decode(const IdxTable& T, uint64_t code, uin
 // 48-bit code of a block given as decoded fields that were already checked to
 // form a point of the ball; false if its sign pattern or codeword is not one
 // the index can name (not a lattice point).
-__host__ __device__ inline bool idx_encode(const IdxTable& T, uint16_t cls, uint8_t gain,
+inline bool idx_encode(const IdxTable& T, uint16_t cls, uint8_t gain,
                                            uint32_t smask, const uint8_t* level, uint64_t* code) {
   const IdxClass& c = T.cls[cls];
   uint64_t r;

@@ -262,9 +262,10 @@ __device__ __forceinline__ uint32_t g70_place(uint32_t p, uint32_t p4) {
 // subnormal whole numbers that the other layouts' tables give.  The placed
 // planes put the coordinates of pairs (r, 16 + r) and (8 + r, 12 + r) in the
 // four low nibbles of n[r], those of (4 + r, 20 + r) in two high ones, which
-// two of the n share one lookup for.  The kernel is bound by vector
-// instructions: 2.3 of them a pair here, against 4.3 with a selector of each
-// pair's own (17408×5120: 18.8 against 21.2 µs).
+// two of the n share one lookup for.  2.3 vector instructions a pair, against 4.3
+// with a selector of each pair's own (17408×5120: 18.8 against 21.2 µs; a launch
+// of one or two units a wave pays 0.1 µs for the tables' conversion, 64×512 4.2 ->
+// 4.3).
 __device__ __forceinline__ void golay70_core(uint32_t r0, uint32_t r1, uint32_t r2, uint32_t side,
                                              uint32_t tlo, uint32_t thi, uint32_t h[12]) {
   const uint32_t c0 = g70_place(align(r1, r0, kG70C0Pos), align(r1, r0, kG70C0Pos + 4));

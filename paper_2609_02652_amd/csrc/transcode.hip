@@ -71,7 +71,7 @@ struct TranscodeArgs {
   uint64_t main_bytes, runs;
   uint64_t n;                       // blocks
   uint64_t tile_blocks;             // blocks of a full tile
-  uint64_t M, nb, tiles;
+  uint64_t nb, tiles;
   uint32_t C, R, rows_last;
   uint32_t inv_tile, inv_unit, inv_unit_last;   // 2^32 / d, rounded up
 };
@@ -384,7 +384,6 @@ TranscodeArgs slot_args(const Geometry& geo) {
   TranscodeArgs a = {};
   a.n = (uint64_t)geo.M * (uint64_t)geo.nb;
   a.tile_blocks = (uint64_t)geo.R * (uint64_t)geo.nb;
-  a.M = (uint64_t)geo.M;
   a.nb = (uint64_t)geo.nb;
   a.C = (uint32_t)geo.C;
   a.R = (uint32_t)geo.R;
