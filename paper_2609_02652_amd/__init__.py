@@ -8,6 +8,8 @@ memory and streams.  Importing it fails loudly if the library is not built.
 """
 from __future__ import annotations
 
+from contextlib import nullcontext
+
 import numpy as np
 
 from . import _lib
@@ -42,9 +44,11 @@ def _stream(stream):
 
 def _dev(arr: np.ndarray, device):
     torch = _torch()
-    # a tensor over a read-only array (memory-mapped weights) would warn, or
-    # raise where warnings are errors
-    arr = np.require(arr, requirements=("C", "W")).view(np.uint8)
+    arr = np.ascontiguousarray(arr).view(np.uint8)
+    if not arr.flags.writeable:
+        # a tensor over a read-only array (memory-mapped weights) would warn, or
+        # raise where warnings are errors
+        arr = arr.copy()
     return torch.from_numpy(arr).to(device)
 
 
@@ -90,11 +94,11 @@ class LeechMatrix:
             raise ValueError("codes must be a contiguous int64 tensor [M, nb]")
         M, nb = codes.shape
         desc = planes14_desc(M, nb * 24)
-        rowmajor = np.ascontiguousarray(scale_rowmajor, np.float16).reshape(-1)[: M * nb]
-        if rowmajor.size < M * nb:
+        if np.asarray(scale_rowmajor).size < M * nb:
             raise ValueError("scale_rowmajor must hold one fp16 scale per block")
         dev = codes.device
-        with torch.cuda.device(dev):
+        here = dev.type == "cuda" and dev.index == torch.cuda.current_device()
+        with nullcontext() if here else torch.cuda.device(dev):
             main = torch.empty(desc.main_bytes, dtype=torch.uint8, device=dev)
             bad = torch.empty(1, dtype=torch.int32, device=dev)
             # A caller's stream runs between two waits: for the codes and the
@@ -116,7 +120,8 @@ class LeechMatrix:
                     torch.cuda.current_stream().wait_stream(side)
             # the scales take their storage order on the device; on the current
             # stream, like the copy: the wait for `bad` covers everything
-            rows = _dev(rowmajor, dev)
+            rowmajor = np.ascontiguousarray(scale_rowmajor, np.float16).reshape(-1)
+            rows = _dev(rowmajor[: M * nb], dev)
             scale = torch.empty_like(rows)
             _lib.layout_scales_device(desc, rows.data_ptr(), scale.data_ptr(), current)
             n_bad = int(bad.item())

@@ -395,9 +395,9 @@ def test_from_codes_refuses_short_scales_before_any_launch(cb, monkeypatch):
     class Table:
         index = torch.zeros(16, dtype=torch.uint8)
 
-    with pytest.raises(ValueError, match="one fp16 scale per block"):
-        P.LeechMatrix.from_codes(Table, torch.zeros((4, 3), dtype=torch.int64),
-                                 np.zeros(11, np.float16))
+    for short in (np.zeros(11, np.float16), torch.zeros(11, dtype=torch.float16), [0.0] * 11):
+        with pytest.raises(ValueError, match="one fp16 scale per block"):
+            P.LeechMatrix.from_codes(Table, torch.zeros((4, 3), dtype=torch.int64), short)
     assert not launched
 
 
