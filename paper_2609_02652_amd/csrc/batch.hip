@@ -282,13 +282,13 @@ __global__ __launch_bounds__(kThreads, WPS) void batch_kernel(BatchArgs a) {
       const uint32_t idx = __umul24(g, lane_group) + lane_row + j - ((int)g == glast ? lane_skip : 0u);
       // Past the last column: a scale of zero, zero activations, and a record of
       // zeros, which nothing is read for (so the class factors have to be
-      // finite, see launch_batch_mx), or with three columns a unit the buffer's
-      // first record: its tiles take the general path for every step, and the
-      // 32 × 16 one spills four registers with the other choice (5120×17408, 16
-      // activations: 24.7 µs here, 27.5; the other widths lose 2–5% this way).
+      // finite, see launch_batch_mx), or in the 32 × 16 tile of three columns the
+      // buffer's first record: it takes the general path for every step, and
+      // spills four registers with the other choice (5120×17408, 16 activations:
+      // 24.7 µs here, 27.5; other tiles lose up to 5% this way).
       const bool live = (int)j < nb;
       uint32_t off = __umul24(idx, (uint32_t)kPlanes14Bytes);
-      if constexpr (C == 3) {
+      if constexpr (C == 3 && NB == 16) {
         off = live ? off : 0u;
         vo = step < steps ? off & ~3u : kOutOfRange;
       } else {
